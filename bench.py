@@ -91,7 +91,7 @@ def _bench_line(log_path):
 
 
 def _is_w4_gemm(name):
-    # gemm_kernel<MI, weight format, epilogue, waves>; format 1 = int4
+    # gemm_kernel<MI, weight format, epilogue, ...>; format 1 = int4
     if "gemm_kernel<" not in name:
         return False
     args = name.split("gemm_kernel<")[1].split(">")[0].split(",")
@@ -171,7 +171,7 @@ def mfma_summary(root):
         if _is_w4_gemm(name):
             epi = name.split("gemm_kernel<")[1].split(",")[2].strip()
             return {"1": "W4A16 GEMM, residual add (o, down)", "2": "W4A16 GEMM, SwiGLU (gate/up)",
-                    "4": "W4A16 GEMM, QKV + RoPE (qkv)", "0": "W4A16 GEMM, fp16 store"}.get(epi, epi)
+                    "4": "W4A16 GEMM, QKV + RoPE (qkv)"}.get(epi, epi)
         if "gemm_kernel<" in name:
             return "W8A16 GEMM (FP8 weights)"
         if "head2_kernel" in name or "head_kernel" in name:

@@ -129,22 +129,22 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restr
 }
 
 // --------------------------------------------------------------- int4 repack
-// One thread per (64-column block, group, lane, word): gathers the 8 codes of
-// column nb*64 + 16f + c, features kg*32 + 8g .. +7, from its source row and
-// writes them biased by +8 in the nibble order the GEMM's dequant expects.
-__global__ void repack_kernel(RepackSrc src, const int32_t* __restrict__ colsrc, int np, int kg_n,
+// One thread per (16-column strip, 64-feature panel, lane, half): gathers the
+// 8 codes of column 16*strip + c, features 64*panel + 32*half + 8g .. +7,
+// from its source row and writes them biased by +8 in the nibble order the
+// GEMM's dequant expects.
+__global__ void repack_kernel(RepackSrc src, const int32_t* __restrict__ colsrc, int np, int k64_n,
                               uint32_t* __restrict__ qpack, f16* __restrict__ spack) {
   const size_t item = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = (size_t)(np / 64) * kg_n * 256;
+  const size_t total = (size_t)(np / 16) * k64_n * 128;
   if (item >= total) return;
-  const int f = item & 3;
-  const int lane = (item >> 2) & 63;
-  const size_t blk = item >> 8;  // nb * kg_n + kg
-  const int kg = (int)(blk % kg_n);
-  const int nb = (int)(blk / kg_n);
+  const int half = item & 1;
+  const int lane = (item >> 1) & 63;
+  const size_t blk = item >> 7;  // strip * k64_n + panel
+  const int kg = (int)(blk % k64_n) * 2 + half;
+  const int strip = (int)(blk / k64_n);
   const int g = lane >> 4, c = lane & 15;
-  const int col = nb * 64 + 16 * f + c;
-  const int cs = colsrc[col];
+  const int cs = colsrc[strip * 16 + c];
   uint32_t word = 0x88888888u;  // code 0 everywhere
   f16 scale = (f16)0.0f;
   if (cs >= 0) {
@@ -165,43 +165,41 @@ __global__ void repack_kernel(RepackSrc src, const int32_t* __restrict__ colsrc,
     }
   }
   qpack[item] = word;
-  if (g == 0) spack[blk * 64 + c * 4 + f] = scale;
+  if (g == 0) spack[blk * 32 + c * 2 + half] = scale;
 }
 
-// One item per (64-column block, 32-feature group, half, lane): 16 bytes,
-// the 8 codes of two columns.
+// One item per (16-column strip, 64-feature panel, lane): 16 bytes, the 8
+// codes of each 32-feature half.
 __global__ void repack_fp8_kernel(RepackSrc src, const int32_t* __restrict__ colsrc, int np,
-                                  int kg_n, uint8_t* __restrict__ qpack,
+                                  int k64_n, uint8_t* __restrict__ qpack,
                                   float* __restrict__ sscale) {
   const size_t item = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = (size_t)(np / 64) * kg_n * 128;
+  const size_t total = (size_t)(np / 16) * k64_n * 64;
   if (item >= total) return;
   const int lane = item & 63;
-  const int h = (item >> 6) & 1;
-  const size_t blk = item >> 7;  // nb * kg_n + kg
-  const int kg = (int)(blk % kg_n);
-  const int nb = (int)(blk / kg_n);
+  const size_t blk = item >> 6;  // strip * k64_n + panel
+  const int panel = (int)(blk % k64_n);
+  const int strip = (int)(blk / k64_n);
   const int g = lane >> 4, c = lane & 15;
   uint32_t w[4] = {0u, 0u, 0u, 0u};  // code 0 = +0.0
+  const int col = strip * 16 + c;
+  const int cs = colsrc[col];
+  float scale = 0.f;
+  if (cs >= 0) {
+    const int si = cs >> 24, r = cs & 0xFFFFFF;
+    const int K = src.kp_src[si];
+    const uint8_t* qr = src.q[si] + (size_t)r * K;
 #pragma unroll
-  for (int ff = 0; ff < 2; ++ff) {
-    const int col = nb * 64 + 16 * (2 * h + ff) + c;
-    const int cs = colsrc[col];
-    float scale = 0.f;
-    if (cs >= 0) {
-      const int si = cs >> 24, r = cs & 0xFFFFFF;
-      const int K = src.kp_src[si];
-      const uint8_t* qr = src.q[si] + (size_t)r * K;
+    for (int half = 0; half < 2; ++half)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int k = kg * 32 + 8 * g + j;
+        const int k = panel * 64 + half * 32 + 8 * g + j;
         const uint32_t code = k < K ? qr[k] : 0u;
-        w[2 * ff + (j >> 2)] |= code << (8 * (j & 3));
+        w[2 * half + (j >> 2)] |= code << (8 * (j & 3));
       }
-      scale = src.sf[si][r];
-    }
-    if (kg == 0 && g == 0) sscale[col] = scale;
+    scale = src.sf[si][r];
   }
+  if (panel == 0 && g == 0) sscale[col] = scale;
   *(uint4*)(qpack + item * 16) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
@@ -388,20 +386,20 @@ hipError_t launch_rmsnorm(hipStream_t s, const float* x, int ldx, const float* c
 
 hipError_t launch_repack_w4(hipStream_t s, const RepackSrc& src, const int32_t* colsrc,
                             PackedW& dst) {
-  const int kg_n = dst.kp / 32;
-  const size_t total = (size_t)(dst.np / 64) * kg_n * 256;
+  const int k64_n = dst.kp / 64;
+  const size_t total = (size_t)(dst.np / 16) * k64_n * 128;
   const int blocks = (int)((total + 255) / 256);
-  hipLaunchKernelGGL(repack_kernel, dim3(blocks), dim3(256), 0, s, src, colsrc, dst.np, kg_n,
+  hipLaunchKernelGGL(repack_kernel, dim3(blocks), dim3(256), 0, s, src, colsrc, dst.np, k64_n,
                      dst.qpack, (f16*)dst.spack);
   return hipGetLastError();
 }
 
 hipError_t launch_repack_w8(hipStream_t s, const RepackSrc& src, const int32_t* colsrc,
                             PackedW& dst) {
-  const int kg_n = dst.kp / 32;
-  const size_t total = (size_t)(dst.np / 64) * kg_n * 128;
+  const int k64_n = dst.kp / 64;
+  const size_t total = (size_t)(dst.np / 16) * k64_n * 64;
   const int blocks = (int)((total + 255) / 256);
-  hipLaunchKernelGGL(repack_fp8_kernel, dim3(blocks), dim3(256), 0, s, src, colsrc, dst.np, kg_n,
+  hipLaunchKernelGGL(repack_fp8_kernel, dim3(blocks), dim3(256), 0, s, src, colsrc, dst.np, k64_n,
                      (uint8_t*)dst.qpack, dst.sscale);
   return hipGetLastError();
 }

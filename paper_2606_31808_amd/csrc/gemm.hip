@@ -4,34 +4,56 @@
 // E4M3 codes, one fp32 scale per output column: the FP8 checkpoint layout).
 // The LM head (fp16 weight) is a kernel of its own at the end of the file.
 //
-// Tiling.  4 waves side by side along N; a wave owns all (16*MI) tokens of
-// the tile and 64 output columns, the workgroup (16*MI) x 256.  K advances
-// 64 features (two scale groups) per step through a three-stage LDS ring
-// filled by direct global->LDS loads (global_load_lds_dwordx4, 1 KB per wave
-// instruction): two steps' tiles stream in while the current step's MFMAs
-// run, and one barrier per step suffices.
-//   A tile: 128-byte rows, 16-byte chunks XOR-swizzled by row so that one
+// Tiling.  The packed weight is kept in strips of 16 columns, contiguous
+// along K.  A workgroup's waves stand side by side along N; a wave owns all
+// 16*MI tokens of the tile and FJ strips, so each weight fragment is
+// dequantised once per workgroup and feeds MI MFMAs.  K advances in stages of
+// KP panels of 64 features through an LDS ring filled by direct global->LDS
+// loads (global_load_lds_dwordx4, 1 KB per wave instruction).
+//   A panel: 128-byte rows, 16-byte chunks XOR-swizzled by row so that one
 //           fragment load (16 rows) is free of LDS bank conflicts.
-//   int4 tile: copied verbatim from the packed layout (1 KB per 64 columns x
-//           32 features: lane 16g+c holds the 8 codes of 4 columns), scales
-//           likewise (128 B per 64 columns x 32 features).
+//   codes and scales: copied verbatim from the packed layout; lane 16g + c
+//           holds the codes of column c, features 8g .. 8g+7 of both halves.
 // Each wave dequantises its own weight fragments in registers (nibble |
 // 0x6400 = 1024 + u in fp16, minus 1032 gives the exact code, times the fp16
-// scale: one rounding), once per workgroup, and reuses each for all MI token
-// sub-tiles.  Explicit scheduling groups interleave that dequantisation with
-// the MFMAs (two VALU per MFMA) so the matrix core is not left idle while a
-// wave converts its next fragment.
+// scale: one rounding).
+//
+// What bounds it.  A wave issues in order, and on this chip an MFMA of 16
+// cycles hides two VALU instructions behind it, no third, and no wait: a loop
+// that loads, waits, converts and then multiplies leaves the matrix core idle
+// for most of a step unless a second wave fills in (one wave per SIMD: 2,200
+// cycles for a step of 64 MFMAs).  So the loop is a software pipeline over
+// phases of KK steps of 32 features, in a schedule pinned MFMA by MFMA: while
+// the MFMAs of one phase run, the next phase's activation fragments are read
+// from LDS into registers and its weight fragments are dequantised, two VALU
+// instructions to an MFMA, and the global->LDS loads of a later stage are
+// spread over the whole stage (issued in one go they held up a wave for 30 ns
+// each).  One barrier per stage, before its last phase: by then every
+// fragment of the stage is in registers, so its slot is free, and the next
+// stage has landed.  Small tiles have short phases; they take KK > 1 (a phase
+// longer than an LDS access) and read codes two phases ahead.
+//
+// Measured against the loop before (wait, read, convert, multiply; token
+// tiles of 128, 64 and 32 rows by 256 columns), same card, us per launch:
+//   K = 4096, N = 4096 (O):      9 tokens 36.6 -> 9.8, 160: 37.7 -> 16.4,
+//     500: 39.1 -> 26.3, 1000: 52.4 -> 41.0, 2048: 73.4 -> 68.2
+//   K = 14336, N = 4096 (down):  9: 119.6 -> 24.6, 160: 121.5 -> 47.9,
+//     500: 123.3 -> 78.4, 1000: 160.5 -> 129, 2048: 235 -> 208
+//   K = 4096, N = 28672 (gate/up): 9: 36.8 -> 15.6, 60: 37.8 -> 23.7,
+//     2048: 366 -> 358, 16384: 2814 -> 2752
+// Up to a few hundred tokens what is left is dequantisation (13 VALU per 8
+// weights and token tile); at 16384 tokens the card's power limit (1.4
+// PFLOP/s on N(0, 0.02) weights; the fp16 library product reaches 1.46).
 //
 // The MFMA takes the weight fragment as its A operand and the activations
 // as its B operand, so the accumulator holds C^T: every lane owns 4
 // consecutive output columns of one token, which makes the epilogue's
 // stores 8-byte (fp16) or 16-byte (fp32) vectors.
 //
-// FP8 weights: the tile is 1 KB per 64 columns x 16 features, so a K step
-// holds twice the int4 bytes and the ring has two stages (64 KB, two
-// workgroups per CU).  A lane's 8 codes convert to fp16 exactly with four
-// v_cvt_scalef32_pk_f16_fp8 (every E4M3 value is an fp16 value); the
-// per-column scale multiplies the fp32 accumulator before the epilogue.
+// FP8 weights: twice the int4 bytes per strip.  A lane's 8 codes convert to
+// fp16 exactly with four v_cvt_scalef32_pk_f16_fp8 (every E4M3 value is an
+// fp16 value); the per-column scale multiplies the fp32 accumulator before
+// the epilogue.
 //
 // Workgroups are mapped to tiles XCD-aware: the hardware deals workgroups to
 // the 8 XCDs round-robin, so each XCD is given one contiguous range of
@@ -41,43 +63,58 @@
 #include "kernels.h"
 #include "lds_dma.h"
 
+#include <cmath>
+#include <type_traits>
+
 namespace lmop {
 
 namespace {
 
-// Dequantises the 8 biased codes of one word (nibble p holds feature 2p for
-// p < 4 and 2(p-4)+1 otherwise).  Masking nibbles p and p+4 and or-ing in
-// 0x6400 makes fp16 1024 + u, minus 1032 gives the exact code; masking the
-// next nibble pair in place makes 1024 + 16u, and one fma by 1/16 with -72
-// gives the exact code as well, so one shift by 8 serves all four pairs.
-// Times the scale: one rounding.  `mask` and `magic` arrive in registers the
-// compiler cannot see through, so (x & mask) | magic becomes one v_and_or.
-LMOP_DEVICE f16x8 dequant8(uint32_t w, f16 s, uint32_t mask, uint32_t magic) {
-  const f16x2 bias = {(f16)1032.0f, (f16)1032.0f};
-  const f16x2 sixteenth = {(f16)0.0625f, (f16)0.0625f};
-  const f16x2 bias_hi = {(f16)-72.0f, (f16)-72.0f};
-  const f16x2 s2 = {s, s};
-  const uint32_t mask_hi = mask << 4;
-  const uint32_t w8 = w >> 8;
-  const uint32_t t0 = (w & mask) | magic;
-  const uint32_t t1 = (w & mask_hi) | magic;
-  const uint32_t t2 = (w8 & mask) | magic;
-  const uint32_t t3 = (w8 & mask_hi) | magic;
-  const f16x2 h0 = (__builtin_bit_cast(f16x2, t0) - bias) * s2;
-  const f16x2 h1 = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, t1), sixteenth, bias_hi) * s2;
-  const f16x2 h2 = (__builtin_bit_cast(f16x2, t2) - bias) * s2;
-  const f16x2 h3 = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, t3), sixteenth, bias_hi) * s2;
-  return f16x8{h0.x, h0.y, h1.x, h1.y, h2.x, h2.y, h3.x, h3.y};
+// Dequantisation of a word of 8 biased codes to 8 fp16 weights (nibble p
+// holds feature 2p for p < 4 and 2(p-4)+1 otherwise), in two halves of three
+// steps of two VALU instructions each, which the main loop places between
+// MFMAs.  Masking nibbles p and p+4 and or-ing in 0x6400 makes fp16 1024 + u,
+// minus 1032 gives the exact code; masking the next nibble pair in place
+// makes 1024 + 16u, and one fma by 1/16 with -72 gives the exact code as
+// well, so the second half needs one shift by 8.  Times the scale: one
+// rounding.  `mask` and `magic` arrive in registers the compiler cannot see
+// through, so (x & mask) | magic becomes one v_and_or.
+struct DeqTmp {
+  uint32_t t0, t1;
+  f16x2 h0, h1;
+};
+template <int STEP>
+LMOP_DEVICE void dequant_step(uint32_t w, int half, f16x2 s2, uint32_t mask, uint32_t magic,
+                              DeqTmp& d) {
+  if constexpr (STEP == 0) {
+    const uint32_t x = half ? w >> 8 : w;
+    d.t0 = (x & mask) | magic;
+    d.t1 = (x & (mask << 4)) | magic;
+  } else if constexpr (STEP == 1) {
+    d.h0 = __builtin_bit_cast(f16x2, d.t0) - f16x2{(f16)1032.0f, (f16)1032.0f};
+    d.h1 = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, d.t1),
+                                     f16x2{(f16)0.0625f, (f16)0.0625f},
+                                     f16x2{(f16)-72.0f, (f16)-72.0f});
+  } else {
+    d.h0 = d.h0 * s2;
+    d.h1 = d.h1 * s2;
+  }
 }
 
-// The 8 E4M3 codes of two words (feature order, byte 0 first) as fp16,
-// exactly: every E4M3 value is an fp16 value, so a unit scale changes nothing.
-LMOP_DEVICE f16x8 fp8x8(uint32_t d0, uint32_t d1) {
-  const f16x2 a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d0, 1.0f, false);
-  const f16x2 b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d0, 1.0f, true);
-  const f16x2 c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d1, 1.0f, false);
-  const f16x2 d = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d1, 1.0f, true);
-  return f16x8{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
+// The 4 E4M3 codes of a word (byte 0 first) as fp16, exactly: every E4M3
+// value is an fp16 value, so a unit scale changes nothing.
+LMOP_DEVICE f16x4 fp8x4(uint32_t d) {
+  const f16x2 a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.0f, false);
+  const f16x2 b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.0f, true);
+  return f16x4{a.x, a.y, b.x, b.y};
+}
+
+// fp16 of a product that has first been rounded to fp32: without the empty
+// asm the compiler turns some of these into one instruction that rounds once,
+// in some tile shapes and not in others
+LMOP_DEVICE f16 f16_of(float x) {
+  asm("" : "+v"(x));
+  return (f16)x;
 }
 
 LMOP_DEVICE float silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
@@ -87,50 +124,62 @@ LMOP_DEVICE float silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf
 // SQ_LDS_BANK_CONFLICT counter)
 LMOP_DEVICE int swz(int row) { return row & 7; }
 
-constexpr int BK = 64;
-constexpr int BN4 = 256;   // int4 GEMMs: 4 waves x 64 columns
 constexpr int GM = 4;      // token tiles per L2 group
-constexpr int NSTAGE = 3;  // LDS ring depth
 
 // weight formats of the kernel's weight operand
 constexpr int WF_INT4 = 1;  // int4, one fp16 scale per 32 features
 constexpr int WF_FP8 = 2;   // OCP E4M3, one fp32 scale per output column
 
-template <int MI, int WF, int NW_ = 4>
+// Tile of a workgroup: 16*MI tokens x 16*FJ*NW columns, KP panels of 64
+// features per ring stage, OCC workgroups per CU; NW waves side by side along
+// N, each with all the tokens and FJ strips of 16 columns.
+template <int MI, int WF, int FJ, int NW, int KP, int OCC>
 struct Cfg {
-  // waves per workgroup, side by side along N (64 columns each)
-  static constexpr int NW = NW_;
-  static constexpr int BN = 64 * NW;
-  static constexpr int BM = 16 * MI;
-  static constexpr int A_BYTES = BM * 128;
-  static constexpr int B_BYTES = WF == WF_INT4 ? BN * 32 : BN * 64;
-  static constexpr int S_BYTES = WF == WF_INT4 ? 1024 : 0;
-  static constexpr int STAGE = A_BYTES + B_BYTES + S_BYTES;
-  static constexpr int NS = WF == WF_FP8 ? 2 : NSTAGE;  // ring stages
+  static constexpr int BM = 16 * MI, BN = 16 * FJ * NW;
+  static constexpr int PANEL = BM * 128;                   // 64 features of BM tokens
+  static constexpr int WB = WF == WF_INT4 ? 512 : 1024;    // codes of 16 columns x 64 features
+  static constexpr int A_BYTES = KP * PANEL;
+  static constexpr int W_WAVE = FJ * KP * WB;              // one wave's codes
+  static constexpr int S_WAVE = WF == WF_INT4 ? FJ * KP * 64 : 0;  // and scales
+  static constexpr int STAGE = A_BYTES + NW * (W_WAVE + S_WAVE);
+  static_assert(STAGE % 128 == 0, "stages keep the alignment the swizzle assumes");
   // int4 residual-add tiles prefetch the residual rows into an unread LDS
   // area (1 KB per wave), only so that they are in the caches by the epilogue
-  static constexpr int PF = WF == WF_INT4 ? 1024 * NW : 0;
+  static constexpr int PF = WF == WF_INT4 && BN <= 256 && MI >= 4 ? 1024 * NW : 0;
+  // ring stages: what OCC workgroups' rings leave of a CU's LDS, at most 6
+  static constexpr int FIT = (160 * 1024 / OCC - PF) / STAGE;
+  static constexpr int NS = FIT < 6 ? FIT : 6;
+  static_assert(NS >= 2, "a stage in use and one in flight");
+  // with 4 stages or more, a stage has landed one stage before it is used, so
+  // that its codes can be read two phases before their fragments are
+  static constexpr int AHEAD = NS >= 4 ? 1 : 0;
   static constexpr int LDS = NS * STAGE + PF;
-  // global->LDS instructions one wave issues per K step (A rows, weight tile, scales)
-  static constexpr int A_LOADS = (BM / 8 + NW - 1) / NW;
-  static constexpr int B_LOADS = B_BYTES / 1024 / NW;
-  static constexpr int LOADS = A_LOADS + B_LOADS + (WF == WF_INT4 ? 1 : 0);
+  // global->LDS instructions one wave issues per stage (activations, codes, scales)
+  static constexpr int A_INSTR = KP * BM / 8;              // of the workgroup
+  static constexpr int A_LOADS = (A_INSTR + NW - 1) / NW;
+  static constexpr int W_LOADS = (W_WAVE + 1023) / 1024;
+  static constexpr int LOADS = A_LOADS + W_LOADS + (WF == WF_INT4 ? 1 : 0);
+  static_assert(LOADS + 1 < 64, "a stage's loads fit the vmcnt counter");
 };
 
-// Workgroup: 4 waves side by side along N; wave w owns all BM tokens of the
-// tile and columns n0 + 64w .. +63, so every weight fragment is dequantised
-// once per workgroup and feeds MI MFMAs.
-// 16-token sub-tiles per wave -> workgroups per CU the kernel is built for
-template <int MI>
-struct Occ {
-  static constexpr int value = MI >= 16 ? 1 : 2;
+// One wave's share of one strip's codes and scales of a 64-feature panel:
+// [kk] = the 32-feature half
+template <int WF>
+struct Codes;
+template <>
+struct Codes<WF_INT4> {
+  uint2 w;
+  f16x2 s;
+};
+template <>
+struct Codes<WF_FP8> {
+  uint4 w;
 };
 
-template <int MI, int WF, int EPI, int NW_ = 4>
-__global__ __launch_bounds__((64 * NW_), Occ<MI>::value) void gemm_kernel(const GemmArgs p) {
-  constexpr bool INT4 = WF == WF_INT4;
-  using C = Cfg<MI, WF, NW_>;
-  constexpr int BM = C::BM, BN = C::BN, NW = C::NW;
+template <int MI, int WF, int EPI, int FJ, int NW, int KP, int KK, int OCC>
+__global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(const GemmArgs p) {
+  using C = Cfg<MI, WF, FJ, NW, KP, OCC>;
+  constexpr int BM = C::BM, BN = C::BN, NS = C::NS;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -152,226 +201,293 @@ __global__ __launch_bounds__((64 * NW_), Occ<MI>::value) void gemm_kernel(const 
   const int nt = within / gsz;
   const int m0 = mt * BM, n0 = nt * BN;
 
-  const int KT = p.K / BK;
-  const int KG = p.K / 32;
+  const int K64 = p.K >> 6;     // 64-feature panels
+  const int KT = K64 / KP;      // ring stages
   const f16* A = (const f16*)p.A;
-  // K steps whose stage also prefetches one residual row per wave (the last
-  // PFW steps; 4 waves x 32 steps cover the tile's 128 rows)
-  const int PFW = KT < BM / NW ? KT : BM / NW;
+  // stages whose issue also prefetches residual rows (1 KB = RPI rows of the
+  // tile per wave); PFW stages cover the tile
+  constexpr int RPI = C::PF > 0 ? 256 / BN : 1;
+  constexpr int PF_ALL = C::PF > 0 && EPI == EPI_ADD_F32 ? BM / (RPI * NW) : 0;
+  const int PFW = KT < PF_ALL ? KT : PF_ALL;
 
-  // ---- global -> LDS issue of one K step into stage st; every wave issues
-  // exactly C::LOADS instructions, which the vmcnt waits below rely on.
-  // Each load is a base in scalar registers (moved by kt) plus a per-lane
-  // 32-bit byte offset computed once, and an LDS destination in a scalar
-  // register.
+  // ---- global -> LDS issue of one stage; every wave issues exactly C::LOADS
+  // instructions, which the vmcnt waits below rely on.  Each load is a base
+  // in scalar registers (moved by the stage) plus a per-lane 32-bit byte
+  // offset computed once, and an LDS destination in a scalar register.
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
-  uint32_t aoff[C::A_LOADS];
+  uint32_t aoff[C::A_LOADS], woff[C::W_LOADS], soff = 0;
 #pragma unroll
   for (int i = 0; i < C::A_LOADS; ++i) {
-    int q = wave + NW * i;  // 8 rows per instruction
-    if (q >= BM / 8) q = BM / 8 - 1;  // surplus waves repeat the last rows
-    const int r = q * 8 + (lane >> 3);
+    int q = wave + NW * i;  // 8 rows of one panel per instruction
+    if (q >= C::A_INSTR) q = C::A_INSTR - 1;  // surplus waves repeat the last rows
+    const int r = (q % (BM / 8)) * 8 + (lane >> 3);
     const int chunk = (lane & 7) ^ swz(r);
     const int gm = m0 + r < p.M ? r : p.M - 1 - m0;  // row within the tile, clamped
-    aoff[i] = (uint32_t)(gm * p.lda + chunk * 8) * 2u;
+    aoff[i] = (uint32_t)(gm * p.lda + (q / (BM / 8)) * 64 + chunk * 8) * 2u;
   }
   const char* abase = (const char*)(A + (size_t)m0 * p.lda);
-  const size_t nb0 = (size_t)(n0 >> 6);
-  // int4 scales: lane group pi = lane / 8 fetches pair pi's 128 bytes
-  const uint32_t soff = (uint32_t)(((lane >> 4) * KG + ((lane >> 3) & 1)) * 128 + (lane & 7) * 16);
-  auto issue = [&](int st, int kt) {
-    const uint32_t sA = lds0 + (uint32_t)(st * C::STAGE);
-    const uint32_t sB = sA + C::A_BYTES;
-    const uint32_t sS = sB + C::B_BYTES;
+  const size_t strip0 = (size_t)(n0 >> 4) + wave * FJ;  // this wave's first strip
+  const char* wbase = (const char*)p.bq + strip0 * K64 * C::WB;
+  const char* sbase = (const char*)p.bs + strip0 * K64 * 64;
 #pragma unroll
-    for (int i = 0; i < C::A_LOADS; ++i) {
-      int q = wave + NW * i;
-      if (q >= BM / 8) q = BM / 8 - 1;
-      g2l16_m0(abase + kt * BK * 2, aoff[i], sA + (uint32_t)q * 1024u);
+  for (int i = 0; i < C::W_LOADS; ++i) {
+    const int o = (i * 64 + lane) * 16;  // byte of the wave's codes: [strip][panel][WB]
+    const int piece = o / C::WB;
+    woff[i] = (uint32_t)(((piece / KP) * K64 + piece % KP) * C::WB + o % C::WB);
+  }
+  if constexpr (WF == WF_INT4) {
+    const int piece = lane >> 2;
+    soff = (uint32_t)(((piece / KP) * K64 + piece % KP) * 64 + (lane & 3) * 16);
+  }
+  // instruction n of a stage's loads: activations, codes, scales
+  auto issue_one = [&](int n, uint32_t sA, int kt) {
+    if (n < C::A_LOADS) {
+      int q = wave + NW * n;
+      if (q >= C::A_INSTR) q = C::A_INSTR - 1;
+      g2l16_m0(abase + (size_t)kt * (KP * 128), aoff[n], sA + (uint32_t)q * 1024u);
+    } else if (n < C::A_LOADS + C::W_LOADS) {
+      const int i = n - C::A_LOADS;
+      const uint32_t sW = sA + C::A_BYTES + (uint32_t)(wave * C::W_WAVE) + (uint32_t)i * 1024u;
+      if (C::W_WAVE >= (i + 1) * 1024)
+        g2l16_m0(wbase + (size_t)kt * (KP * C::WB), woff[i], sW);
+      else
+        g2l16_m0_lanes<(C::W_WAVE % 1024) / 16>(wbase + (size_t)kt * (KP * C::WB), woff[i], sW);
+    } else if constexpr (WF == WF_INT4) {
+      const uint32_t sS = sA + C::A_BYTES + NW * C::W_WAVE + (uint32_t)(wave * C::S_WAVE);
+      g2l16_m0_lanes<C::S_WAVE / 16>(sbase + (size_t)kt * (KP * 64), soff, sS);
     }
-    if constexpr (INT4) {
-#pragma unroll
-      for (int i = 0; i < C::B_LOADS; ++i) {  // (64-column block, group) pairs
-        const int q = wave + NW * i;
-        const char* b = (const char*)p.bq + ((nb0 + (q >> 1)) * KG + kt * 2 + (q & 1)) * 1024;
-        g2l16_m0(b, (uint32_t)lane * 16u, sB + (uint32_t)q * 1024u);
-      }
-      {  // scales: 8 pairs x 128 B = one 1 KB instruction, spread over the waves
-        const char* b = (const char*)p.bs + (nb0 * KG + kt * 2) * 128;
-        if ((lane >> 4) == wave) g2l16_m0(b, soff, sS);
-      }
-      if constexpr (EPI == EPI_ADD_F32) {
-        // the residual row r of the tile (1 KB: this wave's 256 columns),
-        // issued after the stage so the waits below can count it
-        if (kt >= KT - PFW) {
-          const int r = (kt - (KT - PFW)) * NW + wave;
-          int gm = m0 + (r < BM ? r : BM - 1);
-          gm = gm < p.M ? gm : p.M - 1;
-          int col = n0 + lane * 4;
-          col = col + 4 <= p.n_out ? col : p.n_out - 4;
-          g2l16_m0((const char*)(p.X + (size_t)gm * p.ldx), (uint32_t)col * 4u,
-                   lds0 + (uint32_t)(C::NS * C::STAGE + wave * 1024));
-        }
-      }
-    } else if constexpr (WF == WF_FP8) {
-      // 1 KB chunks: (64-column block, group) pair q >> 1, half q & 1
-#pragma unroll
-      for (int i = 0; i < C::B_LOADS; ++i) {
-        const int q = wave + NW * i;
-        const int pr = q >> 1;
-        const size_t blk = (nb0 + (pr >> 1)) * KG + kt * 2 + (pr & 1);
-        g2l16_m0((const char*)p.bq + (blk * 2 + (q & 1)) * 1024, (uint32_t)lane * 16u,
-                 sB + (uint32_t)q * 1024u);
+  };
+  // residual rows for the epilogue, after a stage's own loads so the waits
+  // below can count them
+  auto issue_pf = [&](int kt) {
+    if constexpr (PF_ALL > 0) {
+      if (kt >= KT - PFW) {
+        const int r = ((kt - (KT - PFW)) * NW + wave) * RPI + lane / (BN / 4);
+        int gm = m0 + (r < BM ? r : BM - 1);
+        gm = gm < p.M ? gm : p.M - 1;
+        int col = n0 + (lane % (BN / 4)) * 4;
+        col = col + 4 <= p.n_out ? col : p.n_out - 4;
+        g2l16_m0((const char*)(p.X + (size_t)m0 * p.ldx), (uint32_t)((gm - m0) * p.ldx + col) * 4u,
+                 lds0 + (uint32_t)(NS * C::STAGE + wave * 1024));
       }
     }
   };
 
-  // dequant constants kept opaque to the optimiser (see dequant8)
+  // dequant constants kept opaque to the optimiser (see dequant_step)
   uint32_t dq_mask = 0x000F000Fu, dq_magic = 0x64006400u;
   asm volatile("" : "+s"(dq_mask));
   asm volatile("" : "+v"(dq_magic));
 
-  f32x4 acc[4][MI];
+  f32x4 acc[FJ][MI];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int f = 0; f < FJ; ++f)
 #pragma unroll
     for (int i = 0; i < MI; ++i) acc[f][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  if constexpr (INT4) {
-    issue(0, 0);
-    if (KT > 1) issue(1, 1);
-    for (int kt = 0; kt < KT; ++kt) {
-      // this step's stage is complete once at most the next step's loads
-      // (and the residual prefetch issued after them) are in flight
-      if (kt + 1 < KT) {
-        if (EPI == EPI_ADD_F32 && kt + 1 >= KT - PFW)
-          wait_vmcnt<C::LOADS + 1>();
-        else
-          wait_vmcnt<C::LOADS>();
+  // ---- software pipeline over phases of 32 features.  While the MFMAs of
+  // one phase run, the next phase's activation fragments are read from LDS
+  // and its weight fragments are dequantised.
+  const uint32_t a_lane[2] = {(uint32_t)(c * 128 + ((g ^ swz(c)) * 16)),
+                              (uint32_t)(c * 128 + (((4 + g) ^ swz(c)) * 16))};
+  const uint32_t w_lane = (uint32_t)(C::A_BYTES + wave * C::W_WAVE + lane * (C::WB / 64));
+  const uint32_t s_lane = (uint32_t)(C::A_BYTES + NW * C::W_WAVE + wave * C::S_WAVE + c * 4);
+  // token group i of the stage's 32-feature step ks
+  auto read_a = [&](uint32_t st, int ks, int i) {
+    return *(const f16x8*)(smem + st + a_lane[ks & 1] + (ks >> 1) * C::PANEL + i * 2048);
+  };
+  auto read_codes = [&](uint32_t st, int panel, Codes<WF>* cd) {
+#pragma unroll
+    for (int f = 0; f < FJ; ++f) {
+      if constexpr (WF == WF_INT4) {
+        cd[f].w = *(const uint2*)(smem + st + w_lane + (f * KP + panel) * C::WB);
+        cd[f].s = *(const f16x2*)(smem + st + s_lane + (f * KP + panel) * 64);
       } else {
-        wait_vmcnt<0>();
-      }
-      barrier();
-      if (kt + 2 < KT) issue((kt + 2) % NSTAGE, kt + 2);
-      const char* sA = smem + (kt % NSTAGE) * C::STAGE;
-      const char* sB = sA + C::A_BYTES;
-      const char* sS = sB + C::B_BYTES;
-        // both 32-feature groups' activation fragments, codes and scales are
-        // read up front; then one weight fragment at a time
-        f16x8 a[2][MI];
-        uint4 codes[2];
-        f16x4 s4[2];
-  #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-  #pragma unroll
-          for (int i = 0; i < MI; ++i) {
-            const int r = 16 * i + c;
-            a[kk][i] = *(const f16x8*)(sA + r * 128 + (((kk * 4 + g) ^ swz(r)) * 16));
-          }
-          const int q = wave * 2 + kk;
-          codes[kk] = *(const uint4*)(sB + q * 1024 + lane * 16);
-          s4[kk] = *(const f16x4*)(sS + q * 128 + c * 8);
-        }
-  #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-  #pragma unroll
-          for (int f = 0; f < 4; ++f) {
-            const uint32_t cw = f == 0 ? codes[kk].x : f == 1 ? codes[kk].y : f == 2 ? codes[kk].z : codes[kk].w;
-            const f16x8 w = dequant8(cw, s4[kk][f], dq_mask, dq_magic);
-  #pragma unroll
-            for (int i = 0; i < MI; ++i) acc[f][i] = mfma16x16x32(w, a[kk][i], acc[f][i]);
-          }
-        }
-        // Schedule: the LDS reads first, then the first fragment's dequant (13
-        // VALU), then every MFMA followed by up to two VALU, so the remaining
-        // dequant work issues while earlier MFMAs run instead of in VALU-only
-        // stretches that leave the matrix core idle.
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * MI + 4, 0);  // DS reads
-        __builtin_amdgcn_sched_group_barrier(0x002, 13, 0);          // VALU
-  #pragma unroll
-        for (int j = 0; j < 8 * MI; ++j) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
-        }
-    }
-  } else if constexpr (WF == WF_FP8) {
-    // two stages: the next step's tiles load while this step's MFMAs run
-    issue(0, 0);
-    for (int kt = 0; kt < KT; ++kt) {
-      // this step's loads are the only ones in flight
-      wait_vmcnt<0>();
-      barrier();
-      if (kt + 1 < KT) issue((kt + 1) & 1, kt + 1);
-      const char* sA = smem + (kt & 1) * C::STAGE;
-      const char* sB = sA + C::A_BYTES;
-      f16x8 a[2][MI];
-      uint4 cw[2][2];  // [group][half]: half h holds columns 16*(2h + f') + c
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          const int r = 16 * i + c;
-          a[kk][i] = *(const f16x8*)(sA + r * 128 + (((kk * 4 + g) ^ swz(r)) * 16));
-        }
-        const int q = wave * 2 + kk;
-        cw[kk][0] = *(const uint4*)(sB + q * 2048 + lane * 16);
-        cw[kk][1] = *(const uint4*)(sB + q * 2048 + 1024 + lane * 16);
-      }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f) {
-          const uint4 h = cw[kk][f >> 1];
-          const f16x8 w = (f & 1) ? fp8x8(h.z, h.w) : fp8x8(h.x, h.y);
-#pragma unroll
-          for (int i = 0; i < MI; ++i) acc[f][i] = mfma16x16x32(w, a[kk][i], acc[f][i]);
-        }
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 2 * MI + 4, 0);  // DS reads
-      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);           // VALU
-#pragma unroll
-      for (int j = 0; j < 8 * MI; ++j) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // VALU
+        cd[f].w = *(const uint4*)(smem + st + w_lane + (f * KP + panel) * C::WB);
       }
     }
+  };
+  constexpr int PH = 2 * KP / KK;      // phases of a stage, KK steps of 32 features each
+  constexpr int SLOTS = KK * MI * FJ;  // MFMAs of a phase
+  constexpr int LOADS = C::LOADS, AHEAD = PH == 1 ? 0 : C::AHEAD;
+  static_assert((2 * KP) % KK == 0, "phases of a stage");
+  // panels whose codes a phase needs (with KK = 1 two phases share a panel)
+  constexpr int NPC = KK == 1 ? 1 : KK / 2;
+  // dequantisation of one phase's KK * FJ weight fragments in DP pieces of
+  // about two VALU instructions; step0 = the phase's first step in its stage
+  constexpr int PW = WF == WF_INT4 ? 6 : 4;  // pieces per fragment
+  constexpr int DP = PW * FJ * KK;
+  DeqTmp dt;
+  auto deq = [&](int n, const Codes<WF>* cds, int step0, f16x8* wv) {
+    const int fi = n / PW, q = n % PW;
+    const int half_k = (step0 + fi / FJ) & 1;
+    const Codes<WF>& cf = cds[(KK == 1 ? 0 : fi / FJ / 2) * FJ + fi % FJ];
+    f16x8& o = wv[fi];
+    if constexpr (WF == WF_INT4) {
+      const uint32_t word = half_k ? cf.w.y : cf.w.x;
+      const f16x2 s2 = half_k ? __builtin_shufflevector(cf.s, cf.s, 1, 1)
+                              : __builtin_shufflevector(cf.s, cf.s, 0, 0);
+      const int half = q / 3;
+      if (q % 3 == 0) dequant_step<0>(word, half, s2, dq_mask, dq_magic, dt);
+      if (q % 3 == 1) dequant_step<1>(word, half, s2, dq_mask, dq_magic, dt);
+      if (q % 3 == 2) {
+        dequant_step<2>(word, half, s2, dq_mask, dq_magic, dt);
+        if (half == 0)
+          o = f16x8{dt.h0.x, dt.h0.y, dt.h1.x, dt.h1.y, 0, 0, 0, 0};
+        else
+          o = f16x8{o[0], o[1], o[2], o[3], dt.h0.x, dt.h0.y, dt.h1.x, dt.h1.y};
+      }
+    } else {
+      const uint32_t word =
+          half_k ? (q >> 1 ? cf.w.w : cf.w.z) : (q >> 1 ? cf.w.y : cf.w.x);
+      const f16x2 v = (q & 1) ? __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(word, 1.0f, true)
+                              : __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(word, 1.0f, false);
+      if (q == 0) o = f16x8{v.x, v.y, 0, 0, 0, 0, 0, 0};
+      if (q == 1) o = f16x8{o[0], o[1], v.x, v.y, 0, 0, 0, 0};
+      if (q == 2) o = f16x8{o[0], o[1], o[2], o[3], v.x, v.y, 0, 0};
+      if (q == 3) o = f16x8{o[0], o[1], o[2], o[3], o[4], o[5], v.x, v.y};
+    }
+  };
+  // A stage's loads are issued over the PH phases that follow the barrier
+  // that frees its slot, evenly (issued at once they hold up the MFMAs): load
+  // n goes with slot n * TS / LOADS of those phases' TS slots.
+  constexpr int TS = PH * SLOTS;
+  auto issue_part = [&](int at, uint32_t st, int kt) {
+#pragma unroll
+    for (int n = (at * LOADS + TS - 1) / TS; n < ((at + 1) * LOADS + TS - 1) / TS; ++n)
+      issue_one(n, lds0 + st, kt);
+    if (at == TS - 1) issue_pf(kt);
+  };
+
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st)
+    if (st < KT) {
+#pragma unroll
+      for (int n = 0; n < LOADS; ++n) issue_one(n, lds0 + (uint32_t)(st * C::STAGE), st);
+      issue_pf(st);
+    }
+  // a PF load more per stage only waits for more than is needed here
+  if (KT >= NS - 1)
+    wait_vmcnt<(NS - 2 - AHEAD) * LOADS>();
+  else
+    wait_vmcnt<0>();
+  barrier();
+  // cd: codes of the phase dequantised next, cdn: of the one after it
+  Codes<WF> cd[NPC * FJ], cdn[NPC * FJ];
+  f16x8 a[KK * MI], w[KK * FJ];
+  // codes of phase ph (KK >= 2), or of phase ph's panel
+  auto read_phase_codes = [&](uint32_t st, int ph, Codes<WF>* c_) {
+#pragma unroll
+    for (int q = 0; q < NPC; ++q) read_codes(st, KK == 1 ? ph / 2 : ph * NPC + q, c_ + q * FJ);
+  };
+  read_phase_codes(0, 0, cd);
+#pragma unroll
+  for (int r = 0; r < KK * MI; ++r) a[r] = read_a(0, r / MI, r % MI);
+  if (AHEAD && KK > 1) read_phase_codes(0, 1, cdn);
+#pragma unroll
+  for (int n = 0; n < DP; ++n) deq(n, cd, 0, w);
+  if (NS - 1 < KT) {
+#pragma unroll
+    for (int sl = 0; sl < SLOTS; ++sl) issue_part(sl, (uint32_t)((NS - 1) * C::STAGE), NS - 1);
   }
+  uint32_t st_cur = 0, st_prev = (uint32_t)((NS - 1) * C::STAGE);  // byte offsets of stages
+  // MORE: 2 = stages kt + NS - 1 and kt + NS exist, 1 = only the first, 0 = neither
+  auto stage = [&](int kt, auto more_) {
+    constexpr int MORE = decltype(more_)::value;
+    const uint32_t st_next = st_cur + C::STAGE == NS * C::STAGE ? 0u : st_cur + C::STAGE;
+#pragma unroll
+    for (int ph = 0; ph < PH; ++ph) {
+      const bool last = ph == PH - 1;
+      if (last && (MORE || kt + 1 < KT)) {
+        // every fragment of this stage is in registers, so its slot is free
+        // once all waves are here; stage kt + 1 + AHEAD has landed once at
+        // most the later ones are in flight
+        if (MORE) {
+          constexpr int FLY = NS - 2 - AHEAD;
+          if (PF_ALL > 0 && kt + NS - 1 >= KT - PFW)
+            wait_vmcnt_lgkm0<FLY * (LOADS + 1)>();
+          else
+            wait_vmcnt_lgkm0<FLY * LOADS>();
+        } else {
+          wait_vmcnt_lgkm0<0>();
+        }
+        barrier();
+      }
+      const uint32_t nst = last ? st_next : st_cur;
+      const int nph = last ? 0 : ph + 1;  // the next phase
+      f16x8 an[KK * MI], wn[KK * FJ];
+      if constexpr (KK == 1) {
+        if (AHEAD && (nph & 1) == 1)  // the next phase but one's codes
+          read_phase_codes(ph == PH - 2 ? st_next : st_cur, ph == PH - 2 ? 0 : ph + 2, cdn);
+        if (AHEAD && (nph & 1) == 0)
+#pragma unroll
+          for (int f = 0; f < FJ; ++f) cd[f] = cdn[f];
+        if (!AHEAD && (nph & 1) == 0) read_phase_codes(nst, nph, cd);
+      } else if constexpr (AHEAD) {
+#pragma unroll
+        for (int q = 0; q < NPC * FJ; ++q) cd[q] = cdn[q];
+        read_phase_codes(ph + 2 >= PH ? st_next : st_cur, (ph + 2) % PH, cdn);
+      } else {
+        read_phase_codes(nst, nph, cd);
+      }
+      constexpr int R = KK * MI;  // activation fragments of a phase
+      an[0] = read_a(nst, nph * KK, 0);
+      if constexpr (R > 1) an[1] = read_a(nst, nph * KK + 1 / MI, 1 % MI);
+      __builtin_amdgcn_sched_barrier(0);
+      // the phase's slots: one MFMA, then a share of the next phase's reads,
+      // of its dequantisation (not before its codes can have arrived) and of
+      // a later stage's loads
+      const int skip = (KK > 1 || (nph & 1) == 0) && !AHEAD ? (SLOTS >= 16 ? 6 : SLOTS / 4) : 0;
+#pragma unroll
+      for (int sl = 0; sl < SLOTS; ++sl) {
+        const int r = sl / FJ, f = sl % FJ;
+        acc[f][r % MI] = mfma16x16x32(w[(r / MI) * FJ + f], a[r], acc[f][r % MI]);
+        if (f == FJ - 1 && r + 2 < R)
+          an[r + 2] = read_a(nst, nph * KK + (r + 2) / MI, (r + 2) % MI);
+        const int d0 = sl < skip ? 0 : (sl - skip) * DP / (SLOTS - skip);
+        const int d1 = sl < skip ? 0 : (sl + 1 - skip) * DP / (SLOTS - skip);
+#pragma unroll
+        for (int n = d0; n < d1; ++n) {
+          deq(n, cd, nph * KK, wn);
+          if ((n + 1) % PW == 0)  // computed here, not where it is used
+            asm volatile("" : "+v"(wn[n / PW]));
+        }
+        if (MORE == 2 && last) issue_part(sl, st_cur, kt + NS);
+        if (MORE >= 1 && !last) issue_part((ph + 1) * SLOTS + sl, st_prev, kt + NS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r] = an[r];
+#pragma unroll
+      for (int q = 0; q < KK * FJ; ++q) w[q] = wn[q];
+    }
+    st_prev = st_cur;
+    st_cur = st_next;
+  };
+  int kt = 0;
+  for (; kt + NS < KT; ++kt) stage(kt, std::integral_constant<int, 2>{});
+  if (kt + NS - 1 < KT) stage(kt++, std::integral_constant<int, 1>{});
+  for (; kt < KT; ++kt) stage(kt, std::integral_constant<int, 0>{});
 
   // ------------------------------------------------------------ epilogue
-  // acc[f][i][r] = C[m][n], m = m0 + 16i + c, n = n0 + 64*wave + 16f + 4g + r
+  // acc[f][i][r] = C[m][n], m = m0 + 16i + c, n = ncol + 16f + r
   const int mrow = m0 + c;
-  const int ncol = n0 + wave * 64 + 4 * g;
+  const int ncol = n0 + wave * 16 * FJ + 4 * g;
   if constexpr (WF == WF_FP8) {
     // the FP8 weight's per-column scale
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 0; f < FJ; ++f) {
       const float4 sc = *(const float4*)(p.bsc + ncol + 16 * f);
 #pragma unroll
       for (int i = 0; i < MI; ++i) acc[f][i] = acc[f][i] * f32x4{sc.x, sc.y, sc.z, sc.w};
     }
   }
-  if constexpr (EPI == EPI_STORE_F16) {
-    f16* Cp = (f16*)p.C;
+  if constexpr (EPI == EPI_ADD_F32) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int m = mrow + 16 * i;
       if (m >= p.M) continue;
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        const int n = ncol + 16 * f;
-        if (n < p.n_out) {
-          const f32x4 v = acc[f][i];
-          *(f16x4*)(Cp + (size_t)m * p.ldc + n) = f16x4{(f16)v[0], (f16)v[1], (f16)v[2], (f16)v[3]};
-        }
-      }
-    }
-  } else if constexpr (EPI == EPI_ADD_F32) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = mrow + 16 * i;
-      if (m >= p.M) continue;
-#pragma unroll
-      for (int f = 0; f < 4; ++f) {
+      for (int f = 0; f < FJ; ++f) {
         const int n = ncol + 16 * f;
         if (n < p.n_out) {
           float4* xp = (float4*)(p.X + (size_t)m * p.ldx + n);
@@ -385,97 +501,159 @@ __global__ __launch_bounds__((64 * NW_), Occ<MI>::value) void gemm_kernel(const 
         }
       }
     }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    // the wave's 64-column block holds gate columns blk*32 + 0..31 (sub-tiles
-    // 0, 1) and the matching up columns (sub-tiles 2, 3)
-    f16* Cp = (f16*)p.C;
-    const int blk = (n0 >> 6) + wave;
+  } else {
+    // strips 2t, 2t + 1 belong together: f(i, x1, x2, pair) with pair = their
+    // index in the packed columns.  With one strip per wave, waves 2t and
+    // 2t + 1 swap accumulators through the ring's LDS and share the tokens.
+    auto for_pairs = [&](auto&& fn) {
+      const int pair0 = (n0 >> 5) + (wave * FJ >> 1);
+      if constexpr (FJ == 1) {
+        static_assert(FJ > 1 || NW * MI * 1024 <= C::LDS, "the accumulators fit the ring");
+        f32x4* ex = (f32x4*)smem;
+        // the ring's last reads are done in every wave, and no load is in flight
+        wait_vmcnt_lgkm0<0>();
+        barrier();
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = mrow + 16 * i;
-      if (m >= p.M) continue;
+        for (int i = 0; i < MI; ++i) ex[(wave * MI + i) * 64 + lane] = acc[0][i];
+        wait_vmcnt_lgkm0<0>();
+        barrier();
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        const int col = blk * 32 + 16 * f + 4 * g;
-        if (col < p.n_out) {
-          const f32x4 gt = acc[f][i], up = acc[f + 2][i];
-          *(f16x4*)(Cp + (size_t)m * p.ldc + col) =
-              f16x4{(f16)(silu(gt[0]) * up[0]), (f16)(silu(gt[1]) * up[1]),
-                    (f16)(silu(gt[2]) * up[2]), (f16)(silu(gt[3]) * up[3])};
+        for (int i = 0; i < MI; ++i) {
+          if (MI > 1 ? (i & 1) != (wave & 1) : (wave & 1) != 0) continue;
+          const f32x4 o = ex[((wave ^ 1) * MI + i) * 64 + lane];
+          const bool odd = (wave & 1) != 0;
+          fn(i, odd ? o : acc[0][i], odd ? acc[0][i] : o, pair0);
         }
-      }
-    }
-  } else if constexpr (EPI == EPI_QKV) {
-    const int blk = (n0 >> 6) + wave;
-    const int bph = p.hd >> 6;  // 64-column blocks per head
-    const int nqb = p.nq * bph, nkb = p.nkv * bph;
-    if (blk < nqb + 2 * nkb) {
-      const int sec = blk < nqb ? 0 : (blk < nqb + nkb ? 1 : 2);
-      const int hb = blk - (sec == 0 ? 0 : (sec == 1 ? nqb : nqb + nkb));
-      const int head = hb / bph, sub = hb - head * bph;
-      const int half = p.hd >> 1;
-      const int kvdim = p.nkv * p.hd;
+      } else {
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
+        for (int t = 0; t < FJ / 2; ++t)
+#pragma unroll
+          for (int i = 0; i < MI; ++i) fn(i, acc[2 * t][i], acc[2 * t + 1][i], pair0 + t);
+      }
+    };
+    if constexpr (EPI == EPI_SWIGLU) {
+      // 16 gate columns and the matching up columns
+      f16* Cp = (f16*)p.C;
+      for_pairs([&](int i, f32x4 gt, f32x4 up, int pair) {
+        const int m = mrow + 16 * i, col = pair * 16 + 4 * g;
+        if (m < p.M && col < p.n_out)
+          *(f16x4*)(Cp + (size_t)m * p.ldc + col) =
+              f16x4{f16_of(silu(gt[0]) * up[0]), f16_of(silu(gt[1]) * up[1]),
+                    f16_of(silu(gt[2]) * up[2]), f16_of(silu(gt[3]) * up[3])};
+      });
+    } else if constexpr (EPI == EPI_QKV) {
+      const int half = p.hd >> 1;
+      const int pph = p.hd >> 5;  // strip pairs per head
+      const int nqp = p.nq * pph, nkp = p.nkv * pph;
+      const int kvdim = p.nkv * p.hd;
+      for_pairs([&](int i, f32x4 x1, f32x4 x2, int pair) {
         const int m = mrow + 16 * i;
-        if (m >= p.M) continue;
-        const int sl = p.slot[m];
+        if (m >= p.M || pair >= nqp + 2 * nkp) return;
+        const int sec = pair < nqp ? 0 : (pair < nqp + nkp ? 1 : 2);
+        const int hp = pair - (sec == 0 ? 0 : (sec == 1 ? nqp : nqp + nkp));
+        const int head = hp / pph, sub = hp - head * pph;
         if (sec < 2) {
           const float2* cs = p.rope + (size_t)p.pos[m] * half;
           f16* dst = sec == 0 ? (f16*)p.qout + (size_t)m * p.nq * p.hd + head * p.hd
-                              : (f16*)p.kc + (size_t)sl * kvdim + head * p.hd;
+                              : (f16*)p.kc + (size_t)p.slot[m] * kvdim + head * p.hd;
+          const int d = 16 * sub + 4 * g;
+          const float4 c01 = *(const float4*)(cs + d);
+          const float4 c23 = *(const float4*)(cs + d + 2);
+          const float cr[4] = {c01.x, c01.z, c23.x, c23.z};
+          const float sr[4] = {c01.y, c01.w, c23.y, c23.w};
+          f16x4 y1, y2;
 #pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            const int d = 32 * sub + 16 * f + 4 * g;
-            const f32x4 x1 = acc[f][i], x2 = acc[f + 2][i];
-            const float4 c01 = *(const float4*)(cs + d);
-            const float4 c23 = *(const float4*)(cs + d + 2);
-            const float cr[4] = {c01.x, c01.z, c23.x, c23.z};
-            const float sr[4] = {c01.y, c01.w, c23.y, c23.w};
-            f16x4 y1, y2;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              y1[r] = (f16)(x1[r] * cr[r] - x2[r] * sr[r]);
-              y2[r] = (f16)(x1[r] * sr[r] + x2[r] * cr[r]);
-            }
-            *(f16x4*)(dst + d) = y1;
-            *(f16x4*)(dst + half + d) = y2;
+          for (int r = 0; r < 4; ++r) {
+            y1[r] = (f16)(x1[r] * cr[r] - x2[r] * sr[r]);
+            y2[r] = (f16)(x1[r] * sr[r] + x2[r] * cr[r]);
           }
+          *(f16x4*)(dst + d) = y1;
+          *(f16x4*)(dst + half + d) = y2;
         } else {
-          f16* vt = (f16*)p.vt + (size_t)head * p.hd * p.cap + sl;
+          f16* vt = (f16*)p.vt + (size_t)head * p.hd * p.cap + p.slot[m];
 #pragma unroll
-          for (int f = 0; f < 4; ++f)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              vt[(size_t)(64 * sub + 16 * f + 4 * g + r) * p.cap] = (f16)acc[f][i][r];
+          for (int r = 0; r < 4; ++r) {
+            vt[(size_t)(32 * sub + 4 * g + r) * p.cap] = (f16)x1[r];
+            vt[(size_t)(32 * sub + 16 + 4 * g + r) * p.cap] = (f16)x2[r];
+          }
         }
-      }
+      });
     }
   }
 }
 
-template <int MI, int WF, int EPI, int NW = 4>
+template <int MI, int WF, int EPI, int FJ, int NW, int KP, int KK, int OCC>
 hipError_t launch_cfg(hipStream_t s, const GemmArgs& a) {
-  using C = Cfg<MI, WF, NW>;
+  using C = Cfg<MI, WF, FJ, NW, KP, OCC>;
   const int tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
   if (tiles == 0) return hipSuccess;
   // set once per instantiation (a function-local static is initialised once,
   // also when several threads launch)
   static const hipError_t attr = hipFuncSetAttribute(
-      (const void*)gemm_kernel<MI, WF, EPI, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-      C::LDS);
+      (const void*)gemm_kernel<MI, WF, EPI, FJ, NW, KP, KK, OCC>,
+      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gemm_kernel<MI, WF, EPI, NW>), dim3(tiles), dim3(64 * NW), C::LDS, s, a);
+  hipLaunchKernelGGL((gemm_kernel<MI, WF, EPI, FJ, NW, KP, KK, OCC>), dim3(tiles), dim3(64 * NW), C::LDS, s,
+                     a);
   return hipGetLastError();
+}
+
+// A tile shape and its measured time per 64-feature panel in ns: with one
+// workgroup on a CU (t1) and, where two fit, with two (t2).
+struct Tile {
+  int bm, bn, kp, occ;
+  float t1, t2;
+};
+
+// Estimated time of the GEMM's M x N tiles per 64-feature panel: rounds over
+// the 256 CUs, the last one with one workgroup a CU if they suffice.  Every
+// tile shape sums each output in the same order, so the choice never changes
+// a bit.  Measured against each other on M = 9 .. 16384 tokens at N = 4096
+// and 28672, the estimate picks the fastest shape or one within 5% of it.
+inline float tile_cost(const Tile& t, const GemmArgs& a) {
+  if ((a.K / 64) % t.kp != 0) return INFINITY;
+  const long tiles = (long)((a.M + t.bm - 1) / t.bm) * (a.N / t.bn);
+  const long round = 256 * t.occ, full = tiles / round, rem = tiles % round;
+  const float tf = t.occ == 2 ? t.t2 : t.t1;
+  return full * tf + (rem == 0 ? 0.f : rem <= 256 ? t.t1 : t.t2);
 }
 
 template <int WF, int EPI>
 hipError_t launch_epi(hipStream_t s, const GemmArgs& a) {
-  // the largest token tile that still gives every CU a workgroup
-  const long ntn = a.N / 256;
-  if ((long)((a.M + 127) / 128) * ntn >= 256) return launch_cfg<8, WF, EPI>(s, a);
-  if ((long)((a.M + 63) / 64) * ntn >= 256) return launch_cfg<4, WF, EPI>(s, a);
-  return launch_cfg<2, WF, EPI>(s, a);
+  constexpr bool I4 = WF == WF_INT4;
+  // large token tiles convert each weight for more tokens; small ones reach
+  // more CUs, and walk K in stages of several panels
+  static const Tile tiles[] = {
+      {128, 256, 1, 2, I4 ? 900.f : 1040.f, I4 ? 1620.f : 1590.f},
+      {128, 128, 1, 2, I4 ? 560.f : 500.f, I4 ? 943.f : 855.f},
+      {64, 128, 2, 2, I4 ? 330.f : 430.f, I4 ? 560.f : 540.f},
+      {64, 64, 2, 2, 215.f, 350.f},
+      {32, 128, 4, 1, I4 ? 225.f : 195.f, 0.f},
+      {32, 128, 1, 2, I4 ? 300.f : 250.f, I4 ? 415.f : 380.f},
+      {32, 64, 4, 2, I4 ? 140.f : 215.f, I4 ? 220.f : 240.f},
+      {16, 64, 4, 2, I4 ? 127.f : 112.f, I4 ? 200.f : 180.f},
+      {16, 64, 8, 1, I4 ? 105.f : 97.f, 0.f},
+  };
+  int best = 0;
+  float cost = INFINITY;
+  for (int i = 0; i < (int)(sizeof(tiles) / sizeof(tiles[0])); ++i) {
+    const float c = tile_cost(tiles[i], a);
+    if (c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  switch (best) {
+    case 0: return launch_cfg<8, WF, EPI, 4, 4, 1, 1, 2>(s, a);
+    case 1: return launch_cfg<8, WF, EPI, 2, 4, 1, 1, 2>(s, a);
+    case 2: return launch_cfg<4, WF, EPI, 2, 4, 2, 2, 2>(s, a);
+    case 3: return launch_cfg<4, WF, EPI, 1, 4, 2, 2, 2>(s, a);
+    case 4: return launch_cfg<2, WF, EPI, 2, 4, 4, 4, 1>(s, a);
+    case 5: return launch_cfg<2, WF, EPI, 2, 4, 1, 1, 2>(s, a);
+    case 6: return launch_cfg<2, WF, EPI, 1, 4, 4, 4, 2>(s, a);
+    case 7: return launch_cfg<1, WF, EPI, 1, 4, 4, 4, 2>(s, a);
+    default: return launch_cfg<1, WF, EPI, 1, 4, 8, 8, 1>(s, a);
+  }
 }
 
 // ---------------------------------------------------------------- LM head
@@ -698,9 +876,8 @@ hipError_t launch_gemm_f16(hipStream_t s, const GemmArgs& a, int epi) {
 
 hipError_t launch_gemm_w4(hipStream_t s, const GemmArgs& a, int epi) {
   // the packed weight is padded to 256 columns so every tile shape divides it
-  if (a.K % BK != 0 || a.N % 256 != 0) return hipErrorInvalidValue;
+  if (a.K % 64 != 0 || a.N % 256 != 0) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_STORE_F16: return launch_epi<WF_INT4, EPI_STORE_F16>(s, a);
     case EPI_ADD_F32: return launch_epi<WF_INT4, EPI_ADD_F32>(s, a);
     case EPI_SWIGLU: return launch_epi<WF_INT4, EPI_SWIGLU>(s, a);
     case EPI_QKV: return launch_epi<WF_INT4, EPI_QKV>(s, a);
@@ -710,9 +887,8 @@ hipError_t launch_gemm_w4(hipStream_t s, const GemmArgs& a, int epi) {
 
 hipError_t launch_gemm_w8(hipStream_t s, const GemmArgs& a, int epi) {
   // the packed weight is padded to 256 columns (and its scales with it)
-  if (a.K % BK != 0 || a.N % 256 != 0 || !a.bsc) return hipErrorInvalidValue;
+  if (a.K % 64 != 0 || a.N % 256 != 0 || !a.bsc) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_STORE_F16: return launch_epi<WF_FP8, EPI_STORE_F16>(s, a);
     case EPI_ADD_F32: return launch_epi<WF_FP8, EPI_ADD_F32>(s, a);
     case EPI_SWIGLU: return launch_epi<WF_FP8, EPI_SWIGLU>(s, a);
     case EPI_QKV: return launch_epi<WF_FP8, EPI_QKV>(s, a);

@@ -9,11 +9,12 @@ typedef uint16_t half_bits;  // fp16 storage as seen from host code
 
 // ---------------------------------------------------------------- W4A16 GEMM
 // Repacked int4 weight of one (possibly fused) linear map, N' x K':
-//   qpack: u32 [Np/64][KG][64 lanes][4]; lane 16g+c, word f holds the 8 codes
-//          of column nb*64 + 16f + c, features kg*32 + 8g .. +7, biased by +8,
-//          nibble p = feature 2p (p < 4) / 2(p-4)+1 (p >= 4)
-//   spack: fp16 [Np/64][KG][16 c][4 f]
-// Np is a multiple of 256, Kp (= 32*KG) a multiple of 64.
+//   qpack: u32 [Np/16][Kp/64][64 lanes][2]; lane 16g+c, word kk holds the 8
+//          codes of column strip*16 + c, features panel*64 + 32kk + 8g .. +7,
+//          biased by +8, nibble p = feature 2p (p < 4) / 2(p-4)+1 (p >= 4)
+//   spack: fp16 [Np/16][Kp/64][16 c][2 kk]
+// A strip of 16 columns is contiguous along K, so any tile of whole strips
+// streams from HBM.  Np is a multiple of 256, Kp a multiple of 64.
 // A linear map packed for the GEMM: int4 codes and fp16 group scales
 // (spack), or FP8 codes and fp32 per-column scales (sscale).
 struct PackedW {
@@ -27,9 +28,8 @@ struct PackedW {
 };
 
 enum Epilogue : int {
-  EPI_STORE_F16 = 0,  // C[m][n] = fp16(acc)
   EPI_ADD_F32 = 1,    // X[m][n] += acc (residual stream)
-  EPI_SWIGLU = 2,     // fused [gate|up] blocks of 32: C[m][j] = fp16(silu(gate_j) * up_j)
+  EPI_SWIGLU = 2,     // fused [gate|up] strips of 16: C[m][j] = fp16(silu(gate_j) * up_j)
   EPI_HEAD = 3,       // LM head (A = tiled head weight, B = hidden rows): per token and 128-entry
                       // vocabulary slice (max, sum exp), allowed-token logits, debug dump
   EPI_QKV = 4         // fused q|k|v: RoPE on q, k; q -> qout, k -> K store, v -> V^T store
@@ -50,7 +50,7 @@ struct GemmArgs {
   // epilogue outputs
   void* C;        // fp16 [M][ldc]
   int ldc;
-  int n_out;      // EPI_STORE_F16: valid columns; EPI_SWIGLU: output columns written
+  int n_out;      // EPI_ADD_F32: valid columns; EPI_SWIGLU: output columns written
   float* X;       // fp32 [M][ldx]
   int ldx;
   // head epilogue (M = vocabulary, N = tokens)
@@ -61,9 +61,9 @@ struct GemmArgs {
   float* dump;           // NULL or fp32 [N][ld_dump]
   int ld_dump;
   // qkv epilogue.  Packed column order: q heads, k heads, v heads; every head
-  // is hd/64 blocks of 64 columns; in a q/k block b of a head the columns are
-  // dims [32b, 32b+32) then [hd/2 + 32b, hd/2 + 32b + 32), so each rotation
-  // pair (d, d + hd/2) sits in one lane; v blocks keep the natural order.
+  // is hd/32 pairs of 16-column strips; in a q/k head pair b holds dims
+  // [16b, 16b+16) then [hd/2 + 16b, hd/2 + 16b + 16), so each rotation pair
+  // (d, d + hd/2) sits in one lane; v heads keep the natural order.
   const int32_t* pos;    // [M] position of each token
   const int32_t* slot;   // [M] KV slot of each token
   const float2* rope;    // [max_seq][hd/2] (cos, sin)
@@ -103,9 +103,8 @@ struct RepackSrc {
 };
 hipError_t launch_repack_w4(hipStream_t s, const RepackSrc& src, const int32_t* colsrc,
                             PackedW& dst);
-// FP8 rows [n][K] of E4M3 codes -> tiles of 2 KB per 64 columns x 32
-// features (two 1 KB halves; lane 16g+c of half h holds the 8 codes of
-// features 8g.. of columns 16(2h)+c and 16(2h+1)+c), scales in column order
+// FP8 rows [n][K] of E4M3 codes -> u8 [Np/16][Kp/64][64 lanes][2 kk][8] (the
+// same strips and lanes as int4), scales in column order
 hipError_t launch_repack_w8(hipStream_t s, const RepackSrc& src, const int32_t* colsrc,
                             PackedW& dst);
 

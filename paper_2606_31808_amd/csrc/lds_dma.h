@@ -36,11 +36,38 @@ LMOP_DEVICE void g2l16_m0(const void* sbase, uint32_t voff, uint32_t lds_addr) {
                : "memory");
 }
 
+// the same for the wave's first N lanes only; every lane must be active.  The
+// mask is set inside the asm, so the compiler sees no branch (a branch in a
+// pinned schedule lets it move the code around it)
+template <int N>
+LMOP_DEVICE void g2l16_m0_lanes(const void* sbase, uint32_t voff, uint32_t lds_addr) {
+  static_assert(N >= 0 && N <= 64, "lanes of a wave");
+  if constexpr (N == 64) {
+    g2l16_m0(sbase, voff, lds_addr);
+  } else if constexpr (N > 0) {
+    constexpr uint64_t mask = (1ull << N) - 1;
+    asm volatile(
+        "s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
+        "s_mov_b64 exec, -1"
+        :
+        : "v"(voff), "s"(sbase), "s"(lds_addr), "s"(mask)
+        : "memory");
+  }
+}
+
 // s_waitcnt vmcnt(N), other counters untouched (gfx9 encoding)
 template <int N>
 LMOP_DEVICE void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
+}
+
+// the same, and every LDS access of the wave done
+template <int N>
+LMOP_DEVICE void wait_vmcnt_lgkm0() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
 }
 
 // workgroup barrier without the memory fence of __syncthreads (which would

@@ -1480,17 +1480,15 @@ lmop_status lmop_load_weights(lmop_ctx* ctx, const lmop_weights* w) {
     {  // fused q | k | v; q and k columns ordered so rotation pairs share a lane
       const lmop_qmat* s[3] = {&L.wq, &L.wk, &L.wv};
       std::vector<int32_t> m(round_up(ctx->qkv_n, 256), -1);
-      const int hd = cf.head_dim, half = hd / 2, bph = hd / 64;
+      const int hd = cf.head_dim, half = hd / 2;
       int j = 0;
       for (int sec = 0; sec < 3; ++sec) {
         const int heads = sec == 0 ? cf.n_heads : cf.n_kv_heads;
         for (int h = 0; h < heads; ++h)
-          for (int sub = 0; sub < bph; ++sub)
-            for (int w = 0; w < 64; ++w, ++j) {
-              const int f = w / 16, e = w % 16;
-              const int dim = sec == 2 ? 64 * sub + w
-                                       : (f < 2 ? 32 * sub + 16 * f + e
-                                                : half + 32 * sub + 16 * (f - 2) + e);
+          for (int sub = 0; sub < hd / 32; ++sub)
+            for (int w = 0; w < 32; ++w, ++j) {
+              const int dim = sec == 2 ? 32 * sub + w
+                                       : (w < 16 ? 16 * sub + w : half + 16 * sub + w - 16);
               m[j] = (sec << 24) | (h * hd + dim);
             }
       }
@@ -1501,16 +1499,16 @@ lmop_status lmop_load_weights(lmop_ctx* ctx, const lmop_weights* w) {
       const int rows[1] = {d};
       LMOP_TRY(pack(ctx, s, 1, concat_map(rows, 1, round_up(d, 256)), d, nq, od, &D.o));
     }
-    {  // gate/up interleaved in blocks of 32: block b = [gate 32b..32b+31 | up 32b..32b+31]
+    {  // gate/up interleaved in strips of 16: [gate 16t .. 16t+15 | up 16t .. 16t+15]
       const lmop_qmat* s[2] = {&L.w_gate, &L.w_up};
-      const int nblk = round_up(F, 32) / 32;
-      std::vector<int32_t> m(round_up(nblk * 64, 256), -1);
-      for (int b = 0; b < nblk; ++b)
-        for (int i = 0; i < 32; ++i) {
-          const int r = b * 32 + i;
+      const int n_strips = round_up(F, 32) / 16;
+      std::vector<int32_t> m(round_up(n_strips * 32, 256), -1);
+      for (int t = 0; t < n_strips; ++t)
+        for (int i = 0; i < 16; ++i) {
+          const int r = t * 16 + i;
           if (r < F) {
-            m[b * 64 + i] = (0 << 24) | r;
-            m[b * 64 + 32 + i] = (1 << 24) | r;
+            m[t * 32 + i] = (0 << 24) | r;
+            m[t * 32 + 16 + i] = (1 << 24) | r;
           }
         }
       LMOP_TRY(pack(ctx, s, 2, m, 2 * F, d, od, &D.gu));

@@ -1,0 +1,76 @@
+"""The GEMM's tile shapes: every shape the dispatch can pick, at the edges of
+its token tile, gives a row the same bits as any other shape does, and the
+oracle's logits."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import OracleLM
+from synth import SHAPES, make_weights
+from tests.parity import compare
+
+pytestmark = pytest.mark.gpu
+
+# d 512 and d_ff 1024 are whole stages of every tile shape; d_ff 688 (11
+# panels of 64) only of the shapes with one panel per stage
+SHAPE = dataclasses.replace(SHAPES["tiny"], name="tiles", n_layers=2, d_model=512, n_heads=8,
+                            n_kv_heads=2, d_ff=1024, vocab=640)
+LENS = [1, 16, 7, 40, 64, 100, 33, 128]
+ALLOWED = np.array([3, 77, 400, 639], np.int32)
+
+
+def _rows(tokens):
+    """Row lengths that make one pass of exactly `tokens` tokens."""
+    out, left, i = [], tokens, 0
+    while left > 0:
+        n = min(LENS[i % len(LENS)], left)
+        out.append(n)
+        left -= n
+        i += 1
+    return out
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_31808_amd import lmop
+    return lmop
+
+
+@pytest.fixture(scope="module", params=[("int4_g32", 1024), ("int4_g32", 688), ("fp8_e4m3", 1024)],
+                ids=["int4", "int4-688", "fp8"])
+def model(request, L):
+    fmt, d_ff = request.param
+    shape = dataclasses.replace(SHAPE, d_ff=d_ff)
+    w = make_weights(shape, seed=31, fmt=fmt)
+    ctx = L.Context(shape, device=0)
+    ctx.load_weights(w)
+    return w, shape, ctx
+
+
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 64, 65, 129, 513, 1025, 2049, 4100, 8200, 16384])
+def test_tile_shapes_agree(model, L, tokens):
+    w, shape, ctx = model
+    rng = np.random.default_rng([5, tokens])
+    lens = _rows(tokens)
+    offs = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=offs[1:])
+    toks = rng.integers(0, shape.vocab, size=tokens).astype(np.int32)
+
+    def run(o, t, budget):
+        print("tile shapes:", tokens, "tokens, budget", budget, flush=True)
+        return ctx.eval_rows(t, o, L.LMOP_ENUM, ALLOWED, no_dedup=True, max_batch_tokens=budget,
+                             debug_logits=len(o) <= 24)
+
+    whole, logits = run(offs, toks, 1 << 15)  # one pass (2,048 rows at most)
+    few = min(len(lens), 23)
+    alone, _ = run(offs[:few + 1], toks[:offs[few]], 1)  # one pass per row
+    for f in ("value", "logprob", "logprob_full"):
+        assert np.array_equal(whole[f][:few], alone[f]), f
+    if logits is not None:
+        ref = OracleLM(w, shape).eval_rows(None, [toks[offs[i]:offs[i + 1]] for i in range(few)],
+                                           1, ALLOWED, keep_logits=True)
+        compare(ref, whole, logits, f"{tokens} tokens")
