@@ -855,6 +855,104 @@ hipError_t launch_head2(hipStream_t s, const GemmArgs& a) {
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- LM head, few rows
+// The same for at most 64 rows, where the head is a stream over its weight
+// (1.05 GB for V = 128256, d = 4096) and the ring's barriers and its 256
+// token rows of loads keep it at 5.0 TB/s.  One wave per vocabulary tile with
+// all rows (F groups of 16): the weight goes straight from memory to
+// registers, D steps of 8 KB ahead per wave and no barrier anywhere, and the
+// token rows come from L2.  Every logit is accumulated in the same order as
+// above.  Measured (us, d 4096 / d 2048, against the ring): 9 rows 213 ->
+// 155 / 128 -> 87 (6.8 TB/s, what a read of this card's memory reaches), 32
+// rows 218 -> 160 / 134 -> 94, 64 rows 231 -> 214 / 143 -> 120.
+template <int F, int D>
+__global__ __launch_bounds__(256, 2) void head_few_kernel(const GemmArgs p) {
+  constexpr int MI = 8;
+  const int lane = threadIdx.x & 63;
+  const int chunk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_chunks = (p.M + kHeadTileRows - 1) / kHeadTileRows;
+  if (chunk >= n_chunks) return;
+  const int g = lane >> 4, c = lane & 15;
+  const int KT = p.K / 32;
+  // lane 16g + c: vocabulary row 16i + c (or token row 16f + c), features 8g ..
+  const f16* W = (const f16*)p.A + (size_t)chunk * KT * (kHeadTileRows * 32) + c * 32 + g * 8;
+  const f16* H[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    const int n = 16 * f + c < p.N ? 16 * f + c : p.N - 1;
+    H[f] = (const f16*)p.bh + (size_t)n * p.ldb + g * 8;
+  }
+  f32x4 acc[F][MI];
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) acc[f][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f16x8 a[D][MI], t[D][F];
+  auto load = [&](int kt, f16x8* av, f16x8* tv) {
+    kt = kt < KT ? kt : KT - 1;  // past the end: read again, never used
+#pragma unroll
+    for (int f = 0; f < F; ++f) tv[f] = *(const f16x8*)(H[f] + kt * 32);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+      av[i] = __builtin_nontemporal_load((const f16x8*)(W + (size_t)kt * (kHeadTileRows * 32) + i * 512));
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, a[d], t[d]);
+  for (int kt = 0; kt < KT; kt += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (kt + d < KT) {
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+          for (int i = 0; i < MI; ++i) acc[f][i] = mfma16x16x32(t[d][f], a[d][i], acc[f][i]);
+      }
+      load(kt + d + D, a[d], t[d]);
+    }
+  }
+  // acc[f][i][r] = z[vocabulary 128 chunk + 16i + c][token 16f + 4g + r]
+  const int v0 = chunk * kHeadTileRows + c;
+  int si[MI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) si[i] = v0 + 16 * i < p.M ? p.sel[v0 + 16 * i] : -1;
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int n = 16 * f + 4 * g + r;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+        if (v0 + 16 * i < p.M) mx = fmaxf(mx, acc[f][i][r]);
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, shfl_xor(mx, o));
+      float sm = 0.f;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int v = v0 + 16 * i;
+        if (v < p.M) {
+          const float z = acc[f][i][r];
+          sm += __expf(z - mx);
+          if (n < p.N) {
+            if (si[i] >= 0) p.zsel[(size_t)n * p.n_sel + si[i]] = z;
+            if (p.dump) p.dump[(size_t)n * p.ld_dump + v] = z;
+          }
+        }
+      }
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) sm += shfl_xor(sm, o);
+      if (c == 0 && n < p.N) p.part[(size_t)n * n_chunks + chunk] = make_float2(mx, sm);
+    }
+}
+
+template <int F, int D>
+hipError_t launch_head_few(hipStream_t s, const GemmArgs& a) {
+  const int n_chunks = (a.M + kHeadTileRows - 1) / kHeadTileRows;
+  if (n_chunks == 0 || a.N == 0) return hipSuccess;
+  hipLaunchKernelGGL((head_few_kernel<F, D>), dim3((n_chunks + 3) / 4), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gemm_f16(hipStream_t s, const GemmArgs& a, int epi) {
@@ -865,6 +963,11 @@ hipError_t launch_gemm_f16(hipStream_t s, const GemmArgs& a, int epi) {
     return hipErrorInvalidValue;
   // per-lane token-row offsets are 32-bit byte offsets within one tile's rows
   if ((size_t)512 * a.ldb * 2 >= (size_t(1) << 31)) return hipErrorInvalidValue;
+  // Up to 64 rows one wave holds all of them (more do not fit its registers);
+  // at 65 rows the ring kernel takes 235 us where 64 rows here take 214.
+  if (a.N <= 16) return launch_head_few<1, 4>(s, a);
+  if (a.N <= 32) return launch_head_few<2, 3>(s, a);
+  if (a.N <= 64) return launch_head_few<4, 2>(s, a);
   // A workgroup's time barely depends on how many of its token rows are
   // real, so the tile that needs fewer token tiles wins; a full 320-token
   // tile runs about 10% longer than a full 256-token one.  Each logit's
