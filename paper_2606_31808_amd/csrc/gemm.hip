@@ -130,6 +130,68 @@ constexpr int GM = 4;      // token tiles per L2 group
 constexpr int WF_INT4 = 1;  // int4, one fp16 scale per 32 features
 constexpr int WF_FP8 = 2;   // OCP E4M3, one fp32 scale per output column
 
+// ---------------------------------------------------------------- epilogues
+// X[m][n .. n+3] += v
+LMOP_DEVICE void add_residual(const GemmArgs& p, int m, int n, f32x4 v) {
+  if (m >= p.M || n >= p.n_out) return;
+  float4* xp = (float4*)(p.X + (size_t)m * p.ldx + n);
+  float4 x = *xp;
+  x.x += v[0];
+  x.y += v[1];
+  x.z += v[2];
+  x.w += v[3];
+  *xp = x;
+}
+
+// token m, lane group g: the strips 2 pair, 2 pair + 1 of the packed columns
+// (rows 4g .. 4g+3 of each)
+template <int EPI>
+LMOP_DEVICE void store_pair(const GemmArgs& p, int m, int g, f32x4 x1, f32x4 x2, int pair) {
+  if (m >= p.M) return;
+  if constexpr (EPI == EPI_SWIGLU) {
+    // 16 gate columns and the matching up columns
+    const int col = pair * 16 + 4 * g;
+    if (col < p.n_out)
+      *(f16x4*)((f16*)p.C + (size_t)m * p.ldc + col) =
+          f16x4{f16_of(silu(x1[0]) * x2[0]), f16_of(silu(x1[1]) * x2[1]),
+                f16_of(silu(x1[2]) * x2[2]), f16_of(silu(x1[3]) * x2[3])};
+  } else {
+    static_assert(EPI == EPI_QKV, "paired epilogues");
+    const int half = p.hd >> 1;
+    const int pph = p.hd >> 5;  // strip pairs per head
+    const int nqp = p.nq * pph, nkp = p.nkv * pph;
+    if (pair >= nqp + 2 * nkp) return;
+    const int sec = pair < nqp ? 0 : (pair < nqp + nkp ? 1 : 2);
+    const int hp = pair - (sec == 0 ? 0 : (sec == 1 ? nqp : nqp + nkp));
+    const int head = hp / pph, sub = hp - head * pph;
+    if (sec < 2) {
+      const float2* cs = p.rope + (size_t)p.pos[m] * half;
+      f16* dst = sec == 0 ? (f16*)p.qout + (size_t)m * p.nq * p.hd + head * p.hd
+                          : (f16*)p.kc + (size_t)p.slot[m] * (p.nkv * p.hd) + head * p.hd;
+      const int d = 16 * sub + 4 * g;
+      const float4 c01 = *(const float4*)(cs + d);
+      const float4 c23 = *(const float4*)(cs + d + 2);
+      const float cr[4] = {c01.x, c01.z, c23.x, c23.z};
+      const float sr[4] = {c01.y, c01.w, c23.y, c23.w};
+      f16x4 y1, y2;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        y1[r] = (f16)(x1[r] * cr[r] - x2[r] * sr[r]);
+        y2[r] = (f16)(x1[r] * sr[r] + x2[r] * cr[r]);
+      }
+      *(f16x4*)(dst + d) = y1;
+      *(f16x4*)(dst + half + d) = y2;
+    } else {
+      f16* vt = (f16*)p.vt + (size_t)head * p.hd * p.cap + p.slot[m];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        vt[(size_t)(32 * sub + 4 * g + r) * p.cap] = (f16)x1[r];
+        vt[(size_t)(32 * sub + 16 + 4 * g + r) * p.cap] = (f16)x2[r];
+      }
+    }
+  }
+}
+
 // Tile of a workgroup: 16*MI tokens x 16*FJ*NW columns, KP panels of 64
 // features per ring stage, OCC workgroups per CU; NW waves side by side along
 // N, each with all the tokens and FJ strips of 16 columns.
@@ -483,24 +545,9 @@ __global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(c
   }
   if constexpr (EPI == EPI_ADD_F32) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int m = mrow + 16 * i;
-      if (m >= p.M) continue;
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int f = 0; f < FJ; ++f) {
-        const int n = ncol + 16 * f;
-        if (n < p.n_out) {
-          float4* xp = (float4*)(p.X + (size_t)m * p.ldx + n);
-          float4 x = *xp;
-          const f32x4 v = acc[f][i];
-          x.x += v[0];
-          x.y += v[1];
-          x.z += v[2];
-          x.w += v[3];
-          *xp = x;
-        }
-      }
-    }
+      for (int f = 0; f < FJ; ++f) add_residual(p, mrow + 16 * i, ncol + 16 * f, acc[f][i]);
   } else {
     // strips 2t, 2t + 1 belong together: f(i, x1, x2, pair) with pair = their
     // index in the packed columns.  With one strip per wave, waves 2t and
@@ -531,57 +578,307 @@ __global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(c
           for (int i = 0; i < MI; ++i) fn(i, acc[2 * t][i], acc[2 * t + 1][i], pair0 + t);
       }
     };
-    if constexpr (EPI == EPI_SWIGLU) {
-      // 16 gate columns and the matching up columns
-      f16* Cp = (f16*)p.C;
-      for_pairs([&](int i, f32x4 gt, f32x4 up, int pair) {
-        const int m = mrow + 16 * i, col = pair * 16 + 4 * g;
-        if (m < p.M && col < p.n_out)
-          *(f16x4*)(Cp + (size_t)m * p.ldc + col) =
-              f16x4{f16_of(silu(gt[0]) * up[0]), f16_of(silu(gt[1]) * up[1]),
-                    f16_of(silu(gt[2]) * up[2]), f16_of(silu(gt[3]) * up[3])};
-      });
-    } else if constexpr (EPI == EPI_QKV) {
-      const int half = p.hd >> 1;
-      const int pph = p.hd >> 5;  // strip pairs per head
-      const int nqp = p.nq * pph, nkp = p.nkv * pph;
-      const int kvdim = p.nkv * p.hd;
-      for_pairs([&](int i, f32x4 x1, f32x4 x2, int pair) {
-        const int m = mrow + 16 * i;
-        if (m >= p.M || pair >= nqp + 2 * nkp) return;
-        const int sec = pair < nqp ? 0 : (pair < nqp + nkp ? 1 : 2);
-        const int hp = pair - (sec == 0 ? 0 : (sec == 1 ? nqp : nqp + nkp));
-        const int head = hp / pph, sub = hp - head * pph;
-        if (sec < 2) {
-          const float2* cs = p.rope + (size_t)p.pos[m] * half;
-          f16* dst = sec == 0 ? (f16*)p.qout + (size_t)m * p.nq * p.hd + head * p.hd
-                              : (f16*)p.kc + (size_t)p.slot[m] * kvdim + head * p.hd;
-          const int d = 16 * sub + 4 * g;
-          const float4 c01 = *(const float4*)(cs + d);
-          const float4 c23 = *(const float4*)(cs + d + 2);
-          const float cr[4] = {c01.x, c01.z, c23.x, c23.z};
-          const float sr[4] = {c01.y, c01.w, c23.y, c23.w};
-          f16x4 y1, y2;
+    for_pairs([&](int i, f32x4 x1, f32x4 x2, int pair) {
+      store_pair<EPI>(p, mrow + 16 * i, g, x1, x2, pair);
+    });
+  }
+}
+
+// ---------------------------------------------------------------- few tokens
+// The same product for few tokens, where dequantising is most of the work and
+// the strips alone do not fill the SIMDs (256 strips for N = 4096): a
+// workgroup of 16*MI tokens x FJ strips has 3 waves that only issue loads (a
+// wave that also converts is held up by each load), 8 that dequantise a
+// share of each stage's weight fragments each into LDS, and NC that only
+// multiply (each all tokens x FJ / NC strips, in the same order as above).
+// One barrier per stage of KP panels: while stage kt is multiplied, stage
+// kt + 1 is converted and later ones are loaded.
+// Measured at 9 tokens (us, against the best shape of gemm_kernel): K 4096, N
+// 4096 9.8 -> 6.8; K 14336 24.3 -> 14.8; QKV (K 4096, N 6144) 9.8 -> 8.2.  A
+// stage of 512 features takes about 1,000 cycles: the converters' read,
+// convert and write chain and the barrier, then LDS traffic.
+template <int MI, int WF, int FJ, int NC, int KP>
+struct SplitCfg {
+  static constexpr int BM = 16 * MI, BN = 16 * FJ, NP = 8, NLA = 2;
+  static constexpr int WAVES = 1 + NLA + NP + NC;
+  static constexpr int PANEL = BM * 128;
+  static constexpr int WB = WF == WF_INT4 ? 512 : 1024;
+  static constexpr int A_BYTES = KP * PANEL, C_BYTES = FJ * KP * WB;
+  // codes, then scales (FJ * KP * 64 bytes, padded to a load of 1 KB)
+  static constexpr int W_BYTES = C_BYTES + (WF == WF_INT4 ? 1024 : 0);
+  static constexpr int FRAGS = 2 * FJ * KP;  // weight fragments (1 KB) of a stage
+  static constexpr int FB = FRAGS * 1024;
+  // load instructions of a stage
+  static constexpr int A_LOADS = A_BYTES / 1024 / NLA, W_LOADS = W_BYTES / 1024;  // of a loader
+  static_assert(A_BYTES % (1024 * NLA) == 0, "the same for every loader");
+  // A ring of activation stages (from L2) and a deeper one of weight stages
+  // (from memory: with three stages in flight its latency of about 1.6 us was
+  // the whole time of a stage)
+  static constexpr int NSA = 4;
+  static constexpr int FIT = (160 * 1024 - 2 * FB - NSA * A_BYTES) / W_BYTES;
+  static constexpr int CNT = 63 / W_LOADS + 1;  // loads in flight fit the vmcnt counter
+  static constexpr int NSW = FIT < CNT ? (FIT < 12 ? FIT : 12) : (CNT < 12 ? CNT : 12);
+  static_assert(NSW >= 4 && (NSA - 2) * A_LOADS < 64 && (NSW - 1) * W_LOADS < 64, "rings");
+  static_assert(FJ * KP * 64 <= 1024 && FRAGS % (2 * NP) == 0, "whole panels per converter");
+  static constexpr int LDS = NSA * A_BYTES + NSW * W_BYTES + 2 * FB;
+};
+
+// waits until at most n stages of L loads each are in flight (n <= MAX)
+template <int L, int MAX>
+LMOP_DEVICE void wait_stages(int n) {
+  if constexpr (MAX == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (n >= MAX)
+      wait_vmcnt<MAX * L>();
+    else
+      wait_stages<L, MAX - 1>(n);
+  }
+}
+
+template <int MI, int WF, int EPI, int FJ, int NC, int KP>
+__global__ __launch_bounds__((64 * SplitCfg<MI, WF, FJ, NC, KP>::WAVES), 3) void gemm_split_kernel(const GemmArgs p) {
+  using C = SplitCfg<MI, WF, FJ, NC, KP>;
+  constexpr int BM = C::BM, BN = C::BN, NP = C::NP, NLA = C::NLA, NSA = C::NSA, NSW = C::NSW;
+  constexpr int FC = FJ / NC;  // strips of a consumer
+  static_assert(FJ % NC == 0 && (EPI == EPI_ADD_F32 || FC % 2 == 0), "pairs in one wave");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  // XCD-aware tile order as in gemm_kernel
+  const int ntm = (p.M + BM - 1) / BM, ntn = p.N / BN;
+  const int total = ntm * ntn;
+  const int b = blockIdx.x;
+  const int xcd = b & 7, j = b >> 3;
+  const int per = total >> 3, rem = total & 7;
+  const int logical = xcd * per + (xcd < rem ? xcd : rem) + j;
+  const int grp = logical / (GM * ntn);
+  const int within = logical - grp * GM * ntn;
+  const int gsz = (ntm - grp * GM) < GM ? (ntm - grp * GM) : GM;
+  const int mt = grp * GM + within % gsz;
+  const int nt = within / gsz;
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int K64 = p.K >> 6, KT = K64 / KP;
+  char* const wring = smem + NSA * C::A_BYTES;
+  char* const fb = wring + NSW * C::W_BYTES;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+
+  if (wave == 0) {
+    // ---- loader of the weight stages
+    const size_t strip0 = (size_t)(n0 >> 4);
+    constexpr int CL = C::C_BYTES / 1024;  // loads of codes
+    uint32_t voff[C::W_LOADS];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            y1[r] = (f16)(x1[r] * cr[r] - x2[r] * sr[r]);
-            y2[r] = (f16)(x1[r] * sr[r] + x2[r] * cr[r]);
-          }
-          *(f16x4*)(dst + d) = y1;
-          *(f16x4*)(dst + half + d) = y2;
+    for (int n = 0; n < C::W_LOADS; ++n) {
+      if (n < CL) {
+        const int o = (n * 64 + lane) * 16;  // [strip][panel][WB]
+        const int piece = o / C::WB;
+        voff[n] = (uint32_t)(((piece / KP) * K64 + piece % KP) * C::WB + o % C::WB);
+      } else {
+        // scales; lanes past them repeat the last piece into the padding
+        const int piece = (lane >> 2) < FJ * KP ? lane >> 2 : FJ * KP - 1;
+        voff[n] = (uint32_t)(((piece / KP) * K64 + piece % KP) * 64 + (lane & 3) * 16);
+      }
+    }
+    const char* qb = (const char*)p.bq + strip0 * K64 * C::WB;
+    const char* sb = (const char*)p.bs + strip0 * K64 * 64;
+    auto issue = [&](int slot, int kt) {
+      const uint32_t d = lds0 + (uint32_t)(NSA * C::A_BYTES + slot * C::W_BYTES);
+#pragma unroll
+      for (int n = 0; n < C::W_LOADS; ++n)
+        g2l16_m0(n < CL ? qb + (size_t)kt * (KP * C::WB) : sb + (size_t)kt * (KP * 64), voff[n],
+                 d + (uint32_t)n * 1024u);
+    };
+    const int first = NSW < KT ? NSW : KT;
+    for (int st = 0; st < first; ++st) issue(st, st);
+    wait_stages<C::W_LOADS, NSW - 1>(first - 1);  // stage 0
+    barrier();
+    wait_stages<C::W_LOADS, NSW - 1>(first - 2);  // stage 1
+    int slot = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      // stage kt is converted, so its slot is free
+      barrier();
+      if (kt + NSW < KT) issue(slot, kt + NSW);
+      // stage kt + 2, with those up to kt + NSW in flight
+      const int issued = kt + NSW < KT ? kt + NSW : KT - 1;
+      wait_stages<C::W_LOADS, NSW - 2>(issued - (kt + 2));
+      slot = slot == NSW - 1 ? 0 : slot + 1;
+    }
+    return;
+  }
+  if (wave <= NLA) {
+    // ---- loader of a share of the activation stages
+    uint32_t voff[C::A_LOADS];
+#pragma unroll
+    for (int n = 0; n < C::A_LOADS; ++n) {
+      const int q = (wave - 1) * C::A_LOADS + n;
+      const int r = (q % (BM / 8)) * 8 + (lane >> 3);  // 8 rows of panel q / (BM / 8)
+      const int gm = m0 + r < p.M ? r : p.M - 1 - m0;
+      voff[n] = (uint32_t)(gm * p.lda + (q / (BM / 8)) * 64 + ((lane & 7) ^ swz(r)) * 8) * 2u;
+    }
+    const char* ab = (const char*)((const f16*)p.A + (size_t)m0 * p.lda);
+    auto issue = [&](int slot, int kt) {
+#pragma unroll
+      for (int n = 0; n < C::A_LOADS; ++n)
+        g2l16_m0(ab + (size_t)kt * (KP * 128), voff[n],
+                 lds0 + (uint32_t)(slot * C::A_BYTES + ((wave - 1) * C::A_LOADS + n) * 1024));
+    };
+    const int first = NSA - 1 < KT ? NSA - 1 : KT;
+    for (int st = 0; st < first; ++st) issue(st, st);
+    barrier();
+    wait_stages<C::A_LOADS, NSA - 2>(first - 1);  // stage 0
+    int slot = NSA - 1;
+    for (int kt = 0; kt < KT; ++kt) {
+      // stage kt - 1 is multiplied, so its slot is free
+      barrier();
+      if (kt + NSA - 1 < KT) issue(slot, kt + NSA - 1);
+      // stage kt + 1, with those up to kt + NSA - 1 in flight
+      const int issued = kt + NSA - 1 < KT ? kt + NSA - 1 : KT - 1;
+      wait_stages<C::A_LOADS, NSA - 2>(issued - (kt + 1));
+      slot = slot == NSA - 1 ? 0 : slot + 1;
+    }
+    return;
+  }
+  if (wave < 1 + NLA + NP) {
+    // ---- converter
+    const int cw = wave - 1 - NLA;
+    uint32_t dq_mask = 0x000F000Fu, dq_magic = 0x64006400u;
+    asm volatile("" : "+s"(dq_mask));
+    asm volatile("" : "+v"(dq_magic));
+    // (strip, panel) pairs cw, cw + NP, ...: both fragments of the panel
+    auto convert = [&](uint32_t st, int buf) {
+      constexpr int Q = C::FRAGS / 2 / NP;
+      uint4 w[Q];
+      f16x2 sc[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int piece = cw + NP * q;
+        const char* src = wring + st + piece * C::WB + lane * (C::WB / 64);
+        if constexpr (WF == WF_INT4) {
+          const uint2 x = *(const uint2*)src;
+          w[q] = make_uint4(x.x, x.y, 0u, 0u);
+          sc[q] = *(const f16x2*)(wring + st + C::C_BYTES + piece * 64 + c * 4);
         } else {
-          f16* vt = (f16*)p.vt + (size_t)head * p.hd * p.cap + p.slot[m];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            vt[(size_t)(32 * sub + 4 * g + r) * p.cap] = (f16)x1[r];
-            vt[(size_t)(32 * sub + 16 + 4 * g + r) * p.cap] = (f16)x2[r];
-          }
+          w[q] = *(const uint4*)src;
         }
-      });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        char* out = fb + buf * C::FB + (cw + NP * q) * 2048 + lane * 16;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          f16x8 v;
+          if constexpr (WF == WF_INT4) {
+            const f16x2 s2 = kk ? __builtin_shufflevector(sc[q], sc[q], 1, 1)
+                                : __builtin_shufflevector(sc[q], sc[q], 0, 0);
+            const uint32_t word = kk ? w[q].y : w[q].x;
+            DeqTmp d0, d1;
+            dequant_step<0>(word, 0, s2, dq_mask, dq_magic, d0);
+            dequant_step<0>(word, 1, s2, dq_mask, dq_magic, d1);
+            dequant_step<1>(word, 0, s2, dq_mask, dq_magic, d0);
+            dequant_step<1>(word, 1, s2, dq_mask, dq_magic, d1);
+            dequant_step<2>(word, 0, s2, dq_mask, dq_magic, d0);
+            dequant_step<2>(word, 1, s2, dq_mask, dq_magic, d1);
+            v = f16x8{d0.h0.x, d0.h0.y, d0.h1.x, d0.h1.y, d1.h0.x, d1.h0.y, d1.h1.x, d1.h1.y};
+          } else {
+            const uint32_t lo = kk ? w[q].z : w[q].x, hi = kk ? w[q].w : w[q].y;
+            const f16x2 x0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 1.0f, false);
+            const f16x2 x1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, 1.0f, true);
+            const f16x2 x2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 1.0f, false);
+            const f16x2 x3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, 1.0f, true);
+            v = f16x8{x0.x, x0.y, x1.x, x1.y, x2.x, x2.y, x3.x, x3.y};
+          }
+          *(f16x8*)(out + kk * 1024) = v;
+        }
+      }
+    };
+    barrier();
+    convert(0u, 0);
+    uint32_t st_next = C::W_BYTES;
+    for (int kt = 0; kt < KT; ++kt) {
+      wait_vmcnt_lgkm0<0>();  // stage kt's fragments are written
+      barrier();
+      if (kt + 1 < KT) convert(st_next, (kt + 1) & 1);
+      st_next = st_next + C::W_BYTES == NSW * C::W_BYTES ? 0u : st_next + C::W_BYTES;
+    }
+    return;
+  }
+
+  // ---- consumer
+  const int f0 = (wave - 1 - NLA - NP) * FC;
+  const uint32_t a_lane[2] = {(uint32_t)(c * 128 + ((g ^ swz(c)) * 16)),
+                              (uint32_t)(c * 128 + (((4 + g) ^ swz(c)) * 16))};
+  f32x4 acc[FC][MI];
+#pragma unroll
+  for (int f = 0; f < FC; ++f)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) acc[f][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  barrier();
+  uint32_t st = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    barrier();
+    const char* fr = fb + (kt & 1) * C::FB + lane * 16;
+    // (strip f, panel)'s fragments are at ((f * KP + panel) * 2 + kk) KB
+    f16x8 a[2 * KP][MI], w[2 * KP][FC];
+#pragma unroll
+    for (int ks = 0; ks < 2 * KP; ++ks) {
+#pragma unroll
+      for (int f = 0; f < FC; ++f)
+        w[ks][f] = *(const f16x8*)(fr + (((f0 + f) * KP + (ks >> 1)) * 2 + (ks & 1)) * 1024);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+        a[ks][i] = *(const f16x8*)(smem + st + a_lane[ks & 1] + (ks >> 1) * C::PANEL + i * 2048);
+    }
+    // all reads before the first MFMA (the compiler would read, wait and
+    // multiply step by step)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2 * KP; ++ks)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int f = 0; f < FC; ++f) acc[f][i] = mfma16x16x32(w[ks][f], a[ks][i], acc[f][i]);
+    wait_vmcnt_lgkm0<0>();  // this stage is read, also where an MFMA was moved past the barrier
+    st = st + C::A_BYTES == NSA * C::A_BYTES ? 0u : st + C::A_BYTES;
+  }
+  const int mrow = m0 + c, ncol = n0 + 16 * f0 + 4 * g;
+  if constexpr (WF == WF_FP8) {
+#pragma unroll
+    for (int f = 0; f < FC; ++f) {
+      const float4 sc = *(const float4*)(p.bsc + ncol + 16 * f);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) acc[f][i] = acc[f][i] * f32x4{sc.x, sc.y, sc.z, sc.w};
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if constexpr (EPI == EPI_ADD_F32) {
+#pragma unroll
+      for (int f = 0; f < FC; ++f) add_residual(p, mrow + 16 * i, ncol + 16 * f, acc[f][i]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < FC / 2; ++t)
+        store_pair<EPI>(p, mrow + 16 * i, g, acc[2 * t][i], acc[2 * t + 1][i],
+                        ((n0 >> 4) + f0) / 2 + t);
     }
   }
 }
 
+template <int MI, int WF, int EPI, int FJ, int NC, int KP>
+hipError_t launch_split(hipStream_t s, const GemmArgs& a) {
+  using C = SplitCfg<MI, WF, FJ, NC, KP>;
+  const int tiles = ((a.M + C::BM - 1) / C::BM) * (a.N / C::BN);
+  if (tiles == 0) return hipSuccess;
+  static const hipError_t attr = hipFuncSetAttribute(
+      (const void*)gemm_split_kernel<MI, WF, EPI, FJ, NC, KP>,
+      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((gemm_split_kernel<MI, WF, EPI, FJ, NC, KP>), dim3(tiles),
+                     dim3(64 * C::WAVES), C::LDS, s, a);
+  return hipGetLastError();
+}
 template <int MI, int WF, int EPI, int FJ, int NW, int KP, int KK, int OCC>
 hipError_t launch_cfg(hipStream_t s, const GemmArgs& a) {
   using C = Cfg<MI, WF, FJ, NW, KP, OCC>;
@@ -633,6 +930,8 @@ hipError_t launch_epi(hipStream_t s, const GemmArgs& a) {
       {32, 64, 4, 2, I4 ? 140.f : 215.f, I4 ? 220.f : 240.f},
       {16, 64, 4, 2, I4 ? 127.f : 112.f, I4 ? 200.f : 180.f},
       {16, 64, 8, 1, I4 ? 105.f : 97.f, 0.f},
+      // split between waves: whole strip pairs where the epilogue needs them
+      EPI == EPI_ADD_F32 ? Tile{16, 16, 8, 1, 55.f, 0.f} : Tile{16, 32, 4, 1, 85.f, 0.f},
   };
   int best = 0;
   float cost = INFINITY;
@@ -652,7 +951,12 @@ hipError_t launch_epi(hipStream_t s, const GemmArgs& a) {
     case 5: return launch_cfg<2, WF, EPI, 2, 4, 1, 1, 2>(s, a);
     case 6: return launch_cfg<2, WF, EPI, 1, 4, 4, 4, 2>(s, a);
     case 7: return launch_cfg<1, WF, EPI, 1, 4, 4, 4, 2>(s, a);
-    default: return launch_cfg<1, WF, EPI, 1, 4, 8, 8, 1>(s, a);
+    case 8: return launch_cfg<1, WF, EPI, 1, 4, 8, 8, 1>(s, a);
+    default:
+      if constexpr (EPI == EPI_ADD_F32)
+        return launch_split<1, WF, EPI, 1, 1, 8>(s, a);
+      else
+        return launch_split<1, WF, EPI, 2, 1, 4>(s, a);
   }
 }
 

@@ -74,3 +74,28 @@ def test_tile_shapes_agree(model, L, tokens):
         ref = OracleLM(w, shape).eval_rows(None, [toks[offs[i]:offs[i + 1]] for i in range(few)],
                                            1, ALLOWED, keep_logits=True)
         compare(ref, whole, logits, f"{tokens} tokens")
+
+
+@pytest.mark.parametrize("fmt", ["int4_g32", "fp8_e4m3"])
+@pytest.mark.parametrize("tokens", [1, 9, 16, 17, 40])
+def test_few_tokens_long_k(L, fmt, tokens):
+    """Few tokens over a K loop longer than every ring (128 panels of the down
+    projection): the loaders, converters and consumers of the split kernel
+    wrap their rings, and a row's bits are those of a large batch."""
+    shape = dataclasses.replace(SHAPE, d_model=1024, d_ff=8192, vocab=512)
+    w = make_weights(shape, seed=32, fmt=fmt)
+    ctx = L.Context(shape, device=0)
+    ctx.load_weights(w)
+    rng = np.random.default_rng([6, tokens])
+    toks = rng.integers(0, shape.vocab, size=tokens + 300).astype(np.int32)
+    allowed = np.array([3, 77, 400, 511], np.int32)
+    print("long K:", fmt, tokens, "tokens", flush=True)
+    few, logits = ctx.eval_rows(toks[:tokens], np.array([0, tokens]), L.LMOP_ENUM, allowed,
+                                debug_logits=True)
+    ref = OracleLM(w, shape).eval_rows(None, [toks[:tokens]], 1, allowed, keep_logits=True)
+    compare(ref, few, logits, f"{tokens} tokens")
+    many, many_logits = ctx.eval_rows(toks, np.array([0, tokens, tokens + 300]), L.LMOP_ENUM,
+                                      allowed, debug_logits=True)
+    assert np.array_equal(logits[0], many_logits[0])
+    assert few["logprob_full"][0] == many["logprob_full"][0]
+    ctx.close()
