@@ -24,6 +24,13 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p,
   }
 }
 
+// index[tok[i]] = i
+__global__ __launch_bounds__(256) void index_tokens_kernel(const int32_t* __restrict__ tok, int n,
+                                                           int32_t* __restrict__ index) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) index[tok[i]] = i;
+}
+
 // --------------------------------------------------------------- embedding
 // x[t][:] = fp32(E[tok[t]][:]); one workgroup per token, 8 halves per thread-iteration
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ tok,
@@ -359,6 +366,12 @@ hipError_t launch_fill_u32(hipStream_t s, void* p, size_t n_words, uint32_t valu
   const size_t groups = (n_words + 1023) / 1024;
   const int blocks = (int)(groups < 8192 ? groups : 8192);
   hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks), dim3(256), 0, s, (uint32_t*)p, n_words, value);
+  return hipGetLastError();
+}
+
+hipError_t launch_index_tokens(hipStream_t s, const int32_t* tok, int n, int32_t* index) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(index_tokens_kernel, dim3((n + 255) / 256), dim3(256), 0, s, tok, n, index);
   return hipGetLastError();
 }
 

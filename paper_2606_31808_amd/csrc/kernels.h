@@ -111,6 +111,8 @@ hipError_t launch_repack_w8(hipStream_t s, const RepackSrc& src, const int32_t* 
 // ---------------------------------------------------------------- elementwise
 // p[i] = value for n_words 32-bit words (p 16-byte aligned)
 hipError_t launch_fill_u32(hipStream_t s, void* p, size_t n_words, uint32_t value);
+// index[tok[i]] = i for n distinct tokens (other entries stay)
+hipError_t launch_index_tokens(hipStream_t s, const int32_t* tok, int n, int32_t* index);
 hipError_t launch_embed(hipStream_t s, const int32_t* tok, int T, const half_bits* emb, int d,
                         float* x);
 // x_out[i] = x[idx[i]] (fp32, d), a_out[i] = a[idx[i]] (fp16, da)

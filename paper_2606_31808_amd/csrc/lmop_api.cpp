@@ -35,6 +35,8 @@ constexpr size_t kKeepOwnKvBytes = size_t(1) << 30;
 // library runs on, held until the process ends
 constexpr size_t kNoAllocScratchBytes = size_t(256) << 20;
 constexpr int kMaxBatchRows = 2048;
+// a type's tables up to this size are copied through a staging slot
+constexpr size_t kStagedTableBytes = size_t(1) << 20;
 // own-KV bytes of one integer-decode group (also at most half the free memory)
 constexpr size_t kDecodeGroupBytes = size_t(24) << 30;
 // longest sequence, and largest token budget of one batch; both keep every
@@ -763,6 +765,12 @@ struct Need {
   size_t state_mask = 0;       // bytes of the automaton's state-mask table
 };
 
+// Device bytes of one pass's host-built arrays (see upload_batch)
+size_t batch_in_bytes(size_t T, size_t R, size_t W, size_t last, size_t head_rows) {
+  return T * 12 + R * sizeof(AttnRow) + W * sizeof(int2) + last * 4 +
+         head_rows * (sizeof(void*) + 4) + 16 * 8;
+}
+
 // (name, bytes) of every scratch buffer of a call with these maxima, in
 // layout order; the names are the ones ws_get asks for
 std::vector<std::pair<const char*, size_t>> scratch_items(const lmop_ctx* c, const Need& n) {
@@ -772,28 +780,21 @@ std::vector<std::pair<const char*, size_t>> scratch_items(const lmop_ctx* c, con
   auto add = [&](const char* name, size_t bytes) { it.emplace_back(name, scratch_round(bytes)); };
   // a batch whose rows all have empty suffixes still reads one row of x
   const size_t T = std::max<size_t>(n.T, 1);
-  add("tok", T * 4);
-  add("pos", T * 4);
-  add("slot", T * 4);
-  add("rows", n.R * sizeof(AttnRow));
-  add("work", n.W * sizeof(int2));
+  add("in", batch_in_bytes(T, n.R, n.W, n.last, n.head_rows));
   add("x", T * d * 4);
   add("h", T * d * 2);
   add("q", T * c->nq_dim * 2);
   add("att", T * c->nq_dim * 2);
   add("act", T * c->f64 * 2);
-  add("last", n.last * 4);
   add("xlast", n.last * d * 4);
   add("attlast", n.last * c->nq_dim * 2);
   add("own_kv", n.own_kv);
   if (n.head_rows > 0) {
     const size_t R = n.head_rows;
-    add("head_rowptr", R * sizeof(void*));
     add("head_hn", R * d * 2);
     add("head_part", n.restricted ? sizeof(float2) : R * n_chunks * sizeof(float2));
     add("head_zsel", R * n.n_sel * 4);
     add("head_pick", R * sizeof(HeadPick));
-    add("head_state", R * 4);
     if (n.dump) add("dump", R * V * 4);
   }
   if (n.n_sel > 0) {
@@ -946,7 +947,13 @@ struct Batch {
   int n_work = 0;   // attention work items
   uint16_t* own_kv = nullptr;
   int own_cap = 0;
-  // Tokens whose final hidden state is needed (ws "last"), or 0 = all tokens.
+  // the pass's arrays on the device, copied there by upload_batch
+  const int32_t *tok = nullptr, *pos = nullptr, *slot = nullptr, *last = nullptr;
+  const AttnRow* rows = nullptr;
+  const int2* work = nullptr;
+  const float* const* rowptr = nullptr;  // final hidden state of each head row
+  const int32_t* state = nullptr;        // automaton state of each head row, or NULL
+  // Tokens whose final hidden state is needed (`last`), or 0 = all tokens.
   // With n_last > 0 the last layer's O-projection and MLP run on those tokens
   // only, and their final hidden states land in ws "xlast" [n_last][d].
   int n_last = 0;
@@ -958,21 +965,13 @@ struct Batch {
 };
 
 // One pass of all layers over the T tokens whose ids/positions/slots and row
-// descriptors are already on the device (ws "tok", "pos", "slot", "rows", "work").
+// descriptors are already on the device.
 lmop_status forward(lmop_ctx* c, const Batch& b) {
   const lmop_config& cf = c->cfg;
   const int T = b.T, d = cf.d_model, hd = cf.head_dim;
   if (T == 0) return LMOP_OK;
-  int32_t *tok, *pos, *slot;
-  AttnRow* rows;
-  int2* work;
   float* x;
   uint16_t *h, *q, *att, *act;
-  LMOP_TRY(ws_get(c, "tok", T, &tok));
-  LMOP_TRY(ws_get(c, "pos", T, &pos));
-  LMOP_TRY(ws_get(c, "slot", T, &slot));
-  LMOP_TRY(ws_get(c, "rows", b.R, &rows));
-  LMOP_TRY(ws_get(c, "work", b.n_work, &work));
   LMOP_TRY(ws_get(c, "x", (size_t)T * d, &x));
   LMOP_TRY(ws_get(c, "h", (size_t)T * d, &h));
   LMOP_TRY(ws_get(c, "q", (size_t)T * c->nq_dim, &q));
@@ -980,7 +979,7 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
   LMOP_TRY(ws_get(c, "act", (size_t)T * c->f64, &act));
 
   LMOP_TRY(timed(c, "embed", 0, (double)T * d * 6, [&] {
-    return launch_embed(c->stream, tok, T, c->emb, d, x);
+    return launch_embed(c->stream, b.tok, T, c->emb, d, x);
   }));
   const size_t kv_layer = (size_t)2 * b.own_cap * c->nkv_dim;
   for (int l = 0; l < cf.n_layers; ++l) {
@@ -998,8 +997,8 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
       ga.M = T;
       ga.N = L.qkv.np;
       ga.K = L.qkv.kp;
-      ga.pos = pos;
-      ga.slot = slot;
+      ga.pos = b.pos;
+      ga.slot = b.slot;
       ga.rope = c->rope_tab;
       ga.qout = q;
       ga.kc = kc;
@@ -1019,8 +1018,8 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
     aa.ldq = c->nq_dim;
     aa.out = att;
     aa.ldo = c->nq_dim;
-    aa.rows = rows;
-    aa.work = work;
+    aa.rows = b.rows;
+    aa.work = b.work;
     aa.n_work = b.n_work;
     aa.own_kv = b.own_kv;
     aa.own_cap = b.own_cap;
@@ -1037,12 +1036,10 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
     float* xr = x;
     uint16_t* ar = att;
     if (l == cf.n_layers - 1 && b.n_last > 0) {
-      int32_t* last;
-      LMOP_TRY(ws_get(c, "last", b.n_last, &last));
       LMOP_TRY(ws_get(c, "xlast", (size_t)b.n_last * d, &xr));
       LMOP_TRY(ws_get(c, "attlast", (size_t)b.n_last * c->nq_dim, &ar));
       LMOP_TRY(timed(c, "gather_rows", 0, (double)b.n_last * (d * 8 + c->nq_dim * 4), [&] {
-        return launch_gather_rows(c->stream, last, b.n_last, x, d, xr, att, c->nq_dim, ar);
+        return launch_gather_rows(c->stream, b.last, b.n_last, x, d, xr, att, c->nq_dim, ar);
       }));
       M = b.n_last;
     }
@@ -1075,29 +1072,53 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
   return LMOP_OK;
 }
 
-// Uploads host-built per-token and per-row arrays for one forward pass
-// through staging slot k (which stage_begin has sized); does not wait.
-lmop_status upload_batch(lmop_ctx* c, int k, const std::vector<int32_t>& tok,
+// Uploads the host-built per-token and per-row arrays of one forward pass and
+// its head through staging slot k (which stage_begin has sized) and sets the
+// batch's device pointers; does not wait.  The arrays lie one after the other
+// in one buffer, so that one copy takes them all: a copy of its own for each
+// of the seven cost 3.5 us of the stream and its launch, which a decode step
+// of a few rows waited for (20 us less per decode step of 9 rows).
+lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t>& tok,
                          const std::vector<int32_t>& pos, const std::vector<int32_t>& slot,
                          const std::vector<AttnRow>& rows, const std::vector<int2>& work,
-                         const std::vector<int32_t>& last = {}) {
+                         const std::vector<int32_t>& last = {},
+                         const std::vector<const float*>& rowptr = {},
+                         const std::vector<int32_t>& state = {}) {
   c->stage[k].used = 0;
-  auto put = [&](const char* name, const auto& v) -> lmop_status {
-    using T = typename std::decay_t<decltype(v)>::value_type;
-    T* d;
-    T* h;
-    LMOP_TRY(ws_get(c, name, v.size(), &d));
-    if (v.empty()) return LMOP_OK;
-    LMOP_TRY(stage_put(c, k, v.data(), v.size(), &h));
-    HIP_OK(c, hipMemcpyAsync(d, h, v.size() * sizeof(T), hipMemcpyHostToDevice, c->stream));
-    return LMOP_OK;
+  size_t total = 0;
+  auto place = [&](size_t bytes) {
+    const size_t off = total;
+    total = (total + bytes + 15) & ~(size_t)15;
+    return off;
   };
-  if (!last.empty()) LMOP_TRY(put("last", last));
-  LMOP_TRY(put("tok", tok));
-  LMOP_TRY(put("pos", pos));
-  LMOP_TRY(put("slot", slot));
-  LMOP_TRY(put("rows", rows));
-  LMOP_TRY(put("work", work));
+  auto bytes_of = [](const auto& v) { return v.size() * sizeof(v[0]); };
+  const size_t o_tok = place(bytes_of(tok)), o_pos = place(bytes_of(pos)),
+               o_slot = place(bytes_of(slot)), o_rows = place(bytes_of(rows)),
+               o_work = place(bytes_of(work)), o_last = place(bytes_of(last)),
+               o_rowptr = place(bytes_of(rowptr)), o_state = place(bytes_of(state));
+  char *d, *h;
+  LMOP_TRY(ws_get(c, "in", total, &d));
+  LMOP_TRY(stage_put(c, k, (const char*)nullptr, total, &h));
+  auto put = [&](size_t off, const auto& v) {
+    if (!v.empty()) std::memcpy(h + off, v.data(), bytes_of(v));
+  };
+  put(o_tok, tok);
+  put(o_pos, pos);
+  put(o_slot, slot);
+  put(o_rows, rows);
+  put(o_work, work);
+  put(o_last, last);
+  put(o_rowptr, rowptr);
+  put(o_state, state);
+  if (total > 0) HIP_OK(c, hipMemcpyAsync(d, h, total, hipMemcpyHostToDevice, c->stream));
+  b->tok = (const int32_t*)(d + o_tok);
+  b->pos = (const int32_t*)(d + o_pos);
+  b->slot = (const int32_t*)(d + o_slot);
+  b->rows = (const AttnRow*)(d + o_rows);
+  b->work = (const int2*)(d + o_work);
+  b->last = (const int32_t*)(d + o_last);
+  b->rowptr = (const float* const*)(d + o_rowptr);
+  b->state = state.empty() ? nullptr : (const int32_t*)(d + o_state);
   return LMOP_OK;
 }
 
@@ -1122,33 +1143,25 @@ void add_work(std::vector<int2>& work, int row, int n_q, int G) {
   for (int t = 0; t < tiles; ++t) work.push_back(make_int2(row, t));
 }
 
-// Runs the constrained head over R rows whose final hidden states are at
-// d_rowptr[i]; picks -> host.  dump_host (optional) receives [R][V] logits.
-// Enqueues the head over R rows; the picks land in staging slot k (*picks),
-// valid once the stream has passed this point.
-lmop_status run_head(lmop_ctx* c, int k, int R, const std::vector<const float*>& rowptr,
-                     const int32_t* d_sel, const int32_t* d_allowed, int n_sel, int n_allowed,
-                     bool restricted, HeadPick** picks, float* dump_dev,
-                     const uint8_t* d_state_mask = nullptr,
-                     const std::vector<int32_t>* states = nullptr) {
+// Enqueues the head over the batch's R rows, whose final hidden states are at
+// b.rowptr[i]; the picks land in staging slot k (*picks), valid once the
+// stream has passed this point.  dump_dev (optional) receives [R][V] logits.
+lmop_status run_head(lmop_ctx* c, int k, const Batch& b, const int32_t* d_sel,
+                     const int32_t* d_allowed, int n_sel, int n_allowed, bool restricted,
+                     HeadPick** picks, float* dump_dev, const uint8_t* d_state_mask = nullptr) {
   const lmop_config& cf = c->cfg;
-  const int d = cf.d_model, V = cf.vocab;
+  const int d = cf.d_model, V = cf.vocab, R = b.R;
   const int n_chunks = (V + kHeadVocabChunk - 1) / kHeadVocabChunk;
-  const float** drp;
   uint16_t* hn;
   float2* part;
   float* zsel;
   HeadPick* dpk;
-  LMOP_TRY(ws_get(c, "head_rowptr", R, &drp));
   LMOP_TRY(ws_get(c, "head_hn", (size_t)R * d, &hn));
   LMOP_TRY(ws_get(c, "head_part", restricted ? 1 : (size_t)R * n_chunks, &part));
   LMOP_TRY(ws_get(c, "head_zsel", (size_t)R * n_sel, &zsel));
   LMOP_TRY(ws_get(c, "head_pick", R, &dpk));
-  const float** hrp;
-  LMOP_TRY(stage_put(c, k, rowptr.data(), (size_t)R, &hrp));
-  HIP_OK(c, hipMemcpyAsync(drp, hrp, R * sizeof(float*), hipMemcpyHostToDevice, c->stream));
   LMOP_TRY(timed(c, "rmsnorm_final", 0, (double)R * d * 6, [&] {
-    return launch_rmsnorm(c->stream, nullptr, 0, drp, R, c->final_norm, d, cf.rms_eps, hn, d);
+    return launch_rmsnorm(c->stream, nullptr, 0, b.rowptr, R, c->final_norm, d, cf.rms_eps, hn, d);
   }));
   if (restricted) {
     // only the allowed tokens' logits; the dump's other entries stay NaN
@@ -1179,19 +1192,11 @@ lmop_status run_head(lmop_ctx* c, int k, int R, const std::vector<const float*>&
       }));
     }
   }
-  // per-row automaton states: row r picks within state_mask[states[r]]
-  int32_t* d_states = nullptr;
-  if (states) {
-    int32_t* hst;
-    LMOP_TRY(ws_get(c, "head_state", R, &d_states));
-    LMOP_TRY(stage_put(c, k, states->data(), (size_t)R, &hst));
-    HIP_OK(c, hipMemcpyAsync(d_states, hst, R * sizeof(int32_t), hipMemcpyHostToDevice,
-                             c->stream));
-  }
+  // per-row automaton states: row r picks within state_mask[state[r]]
   LMOP_TRY(timed(c, "head_finalize", 0, 0, [&] {
     return launch_head_finalize(c->stream, part, restricted ? 0 : n_chunks, zsel, n_sel,
-                                n_allowed, d_allowed, R, dpk, d_states,
-                                states ? d_state_mask : nullptr);
+                                n_allowed, d_allowed, R, dpk, b.state,
+                                b.state ? d_state_mask : nullptr);
   }));
   LMOP_TRY(stage_put(c, k, (const HeadPick*)nullptr, (size_t)R, picks));
   HIP_OK(c, hipMemcpyAsync(*picks, dpk, R * sizeof(HeadPick), hipMemcpyDeviceToHost, c->stream));
@@ -1621,7 +1626,7 @@ static lmop_status make_prefixes(lmop_ctx* ctx, const lmop_prefix* parent, const
         t += len[i];
       }
       st = stage_begin(ctx, 0, stage_need(T, R, work.size()));
-      if (st == LMOP_OK) st = upload_batch(ctx, 0, tok, pos, slot, rows, work, last);
+      if (st == LMOP_OK) st = upload_batch(ctx, 0, &b, tok, pos, slot, rows, work, last);
       b.T = T;
       b.R = R;
       b.n_work = (int)work.size();
@@ -1849,8 +1854,9 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
   // state mask table), and the head picks within the row's state's subset.
   const lmop_automaton* aut = type->automaton;
   std::vector<int32_t> allowed;
-  std::vector<int32_t> sel(V, -1);
+  std::vector<int32_t> sel;  // automata: position of each token in the list
   if (is_aut) {
+    sel.assign(V, -1);
     for (int e = 0; e < aut->edge_offset[aut->n_states]; ++e)
       if (sel[aut->edge_token[e]] < 0) {
         sel[aut->edge_token[e]] = (int)allowed.size();
@@ -1863,9 +1869,9 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
   }
   const int n_sel = (int)allowed.size();
   const int n_allowed0 = is_aut ? n_sel : type->n_tokens;
-  for (int i = 0; i < n_sel; ++i) sel[allowed[i]] = i;
   std::vector<uint8_t> state_mask;
   if (is_aut) {
+    for (int i = 0; i < n_sel; ++i) sel[allowed[i]] = i;
     const int S = aut->n_states;
     state_mask.assign((size_t)S * n_sel, 0);
     for (int st = 0; st < S; ++st) {
@@ -2000,19 +2006,42 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
   const auto& group_cap = sch.group_cap;
   budget = sch.budget;
 
+  // The type's tables.  Only the allowed list (and an automaton's state masks)
+  // are copied; sel, an entry per vocabulary token, is built from it on the
+  // device (its copy, 513 KB for V = 128256, and the wait for it took 75 us
+  // of every call).  Small tables go through staging slot 1,
+  // whose next use waits for the copy; larger ones are waited for here.
   int32_t *d_sel, *d_allowed;
   LMOP_TRY(ws_get(ctx, "sel", V, &d_sel));
   LMOP_TRY(ws_get(ctx, "allowed", n_sel, &d_allowed));
-  HIP_OK(ctx, hipMemcpyAsync(d_sel, sel.data(), V * 4, hipMemcpyHostToDevice, ctx->stream));
-  HIP_OK(ctx, hipMemcpyAsync(d_allowed, allowed.data(), n_sel * 4, hipMemcpyHostToDevice,
-                             ctx->stream));
   uint8_t* d_state_mask = nullptr;
-  if (is_aut) {
-    LMOP_TRY(ws_get(ctx, "state_mask", state_mask.size(), &d_state_mask));
-    HIP_OK(ctx, hipMemcpyAsync(d_state_mask, state_mask.data(), state_mask.size(),
-                               hipMemcpyHostToDevice, ctx->stream));
+  if (is_aut) LMOP_TRY(ws_get(ctx, "state_mask", state_mask.size(), &d_state_mask));
+  const size_t table_bytes = (size_t)n_sel * 4 + state_mask.size();
+  const bool staged = table_bytes <= kStagedTableBytes;
+  const int32_t* h_allowed = allowed.data();
+  const uint8_t* h_mask = state_mask.data();
+  if (staged) {
+    int32_t* ha;
+    uint8_t* hm;
+    LMOP_TRY(stage_begin(ctx, 1, table_bytes + 64));
+    LMOP_TRY(stage_put(ctx, 1, allowed.data(), (size_t)n_sel, &ha));
+    LMOP_TRY(stage_put(ctx, 1, state_mask.data(), state_mask.size(), &hm));
+    h_allowed = ha;
+    h_mask = hm;
   }
-  HIP_OK(ctx, hipStreamSynchronize(ctx->stream));
+  HIP_OK(ctx, hipMemcpyAsync(d_allowed, h_allowed, (size_t)n_sel * 4, hipMemcpyHostToDevice,
+                             ctx->stream));
+  if (is_aut)
+    HIP_OK(ctx, hipMemcpyAsync(d_state_mask, h_mask, state_mask.size(), hipMemcpyHostToDevice,
+                               ctx->stream));
+  if (staged)
+    LMOP_TRY(stage_mark(ctx, 1));
+  else
+    HIP_OK(ctx, hipStreamSynchronize(ctx->stream));
+  if (!restricted) {  // the restricted head reads only the allowed list
+    HIP_OK(ctx, launch_fill_u32(ctx->stream, d_sel, (size_t)V, 0xFFFFFFFFu));
+    HIP_OK(ctx, launch_index_tokens(ctx->stream, d_allowed, n_sel, d_sel));
+  }
   const int n_batches = (int)batches.size();
 
   // A batch between enqueue and collect: where its first step's picks land.
@@ -2071,8 +2100,6 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
         last_of[i] = (int)last.size();
         last.push_back(qs[i] + row_len[u0 + i] - 1);
       }
-    LMOP_TRY(stage_begin(ctx, k, stage_need(T, R, work.size())));
-    LMOP_TRY(upload_batch(ctx, k, tok, pos, slot, rows, work, last));
     Batch b;
     b.T = T;
     b.R = R;
@@ -2083,7 +2110,6 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
     for (int i = 0; i < R; ++i)
       b.visible_keys += (double)row_len[u0 + i] * prefix_total(pf[uniq[u0 + i]]) +
                         0.5 * (double)row_len[u0 + i] * (row_len[u0 + i] + 1);
-    LMOP_TRY(forward(ctx, b));
     float* x;
     if (b.n_last > 0)
       LMOP_TRY(ws_get(ctx, "xlast", (size_t)b.n_last * d, &x));
@@ -2097,12 +2123,15 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
       else
         rowptr[i] = x + (size_t)(b.n_last > 0 ? last_of[i] : qs[i] + row_len[u0 + i] - 1) * d;
     }
-    B.dump = nullptr;
-    if (dbg) LMOP_TRY(ws_get(ctx, "dump", (size_t)R * V, &B.dump));
     std::vector<int32_t> st0;
     if (is_aut) st0.assign(R, 0);
-    LMOP_TRY(run_head(ctx, k, R, rowptr, d_sel, d_allowed, n_sel, n_allowed0, restricted, &B.picks,
-                      B.dump, d_state_mask, is_aut ? &st0 : nullptr));
+    LMOP_TRY(stage_begin(ctx, k, stage_need(T, R, work.size())));
+    LMOP_TRY(upload_batch(ctx, k, &b, tok, pos, slot, rows, work, last, rowptr, st0));
+    LMOP_TRY(forward(ctx, b));
+    B.dump = nullptr;
+    if (dbg) LMOP_TRY(ws_get(ctx, "dump", (size_t)R * V, &B.dump));
+    LMOP_TRY(run_head(ctx, k, b, d_sel, d_allowed, n_sel, n_allowed0, restricted, &B.picks, B.dump,
+                      d_state_mask));
     LMOP_TRY(stage_mark(ctx, k));
     B.u0 = u0;
     B.R = R;
@@ -2196,9 +2225,16 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
         sr[q].own_q0 = own_idx;
         add_work(sw, q, 1, G);
       }
-      LMOP_TRY(stage_begin(ctx, 0, stage_need(nl, nl, sw.size())));
-      LMOP_TRY(upload_batch(ctx, 0, st, sp, ss, sr, sw));
+      float* x;
+      LMOP_TRY(ws_get(ctx, "x", (size_t)nl * d, &x));
+      std::vector<const float*> rowptr(nl);
+      for (int q = 0; q < nl; ++q) rowptr[q] = x + (size_t)q * d;
+      std::vector<int32_t> st_live;
+      if (is_aut)
+        for (int q = 0; q < nl; ++q) st_live.push_back(row_state[live[q]]);
       Batch sb;
+      LMOP_TRY(stage_begin(ctx, 0, stage_need(nl, nl, sw.size())));
+      LMOP_TRY(upload_batch(ctx, 0, &sb, st, sp, ss, sr, sw, {}, rowptr, st_live));
       sb.T = nl;
       sb.R = nl;
       sb.n_work = (int)sw.size();
@@ -2207,18 +2243,11 @@ static lmop_status eval_rows_impl(lmop_ctx* ctx, const lmop_prefix* prefix,
       sb.decode = true;
       for (int q = 0; q < nl; ++q) sb.visible_keys += sp[q] + 1;  // position + 1 keys
       LMOP_TRY(forward(ctx, sb));
-      float* x;
-      LMOP_TRY(ws_get(ctx, "x", (size_t)nl * d, &x));
-      std::vector<const float*> rowptr(nl);
-      for (int q = 0; q < nl; ++q) rowptr[q] = x + (size_t)q * d;
       float* dump = nullptr;
       if (dbg) LMOP_TRY(ws_get(ctx, "dump", (size_t)nl * V, &dump));
       HeadPick* picks;
-      std::vector<int32_t> st_live;
-      if (is_aut)
-        for (int q = 0; q < nl; ++q) st_live.push_back(row_state[live[q]]);
-      LMOP_TRY(run_head(ctx, 0, nl, rowptr, d_sel, d_allowed, n_sel, n_sel, restricted, &picks,
-                        dump, d_state_mask, is_aut ? &st_live : nullptr));
+      LMOP_TRY(run_head(ctx, 0, sb, d_sel, d_allowed, n_sel, n_sel, restricted, &picks, dump,
+                        d_state_mask));
       LMOP_TRY(stage_mark(ctx, 0));
       HIP_OK(ctx, hipEventSynchronize(ctx->stage[0].done));
       ctx->stage[0].pending = false;
