@@ -160,7 +160,8 @@ LMOP_DEVICE void store_pair(const GemmArgs& p, int m, int g, f32x4 x1, f32x4 x2,
     const int half = p.hd >> 1;
     const int pph = p.hd >> 5;  // strip pairs per head
     const int nqp = p.nq * pph, nkp = p.nkv * pph;
-    if (pair >= nqp + 2 * nkp) return;
+    pair += p.pair0;
+    if (pair >= p.pair_end) return;
     const int sec = pair < nqp ? 0 : (pair < nqp + nkp ? 1 : 2);
     const int hp = pair - (sec == 0 ? 0 : (sec == 1 ? nqp : nqp + nkp));
     const int head = hp / pph, sub = hp - head * pph;

@@ -72,6 +72,9 @@ struct GemmArgs {
   half_bits* vt;         // layer's V^T store [nkv][hd][cap]
   int cap;
   int nq, nkv, hd;
+  // the first strip pair of the launch and the one past the last it stores, in
+  // the whole projection's packed order
+  int pair0, pair_end;
 };
 
 // Picks the tile shape for M and launches.  Returns hipSuccess or the launch error.

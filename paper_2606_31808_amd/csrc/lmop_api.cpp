@@ -348,10 +348,13 @@ lmop_status stage_mark(lmop_ctx* c, int k) {
 
 // Upper bound of the staging bytes one batch of T tokens and R rows needs.
 size_t stage_need(int T, int R, size_t n_work) {
-  // tokens, positions, slots; per row: attention row, last-token index,
-  // head row pointer, automaton state, pick; work items; alignment
-  return (size_t)T * 12 + (size_t)R * (sizeof(AttnRow) + 8 + sizeof(void*) + sizeof(HeadPick)) +
-         n_work * sizeof(int2) + 16 * 17;
+  // tokens, positions, slots; per row: attention row, last token's index,
+  // position, attention row and work items (G <= 128 per item: at most as
+  // many as the row's own), head row pointer, automaton state, pick; work
+  // items; alignment
+  return (size_t)T * 12 +
+         (size_t)R * (2 * sizeof(AttnRow) + 12 + sizeof(void*) + sizeof(HeadPick)) +
+         2 * n_work * sizeof(int2) + 16 * 20;
 }
 
 // ---------------------------------------------------------------- profiling
@@ -716,13 +719,18 @@ lmop_status pack_fp8(lmop_ctx* c, const lmop_qmat* const* srcs, int n_src,
 }
 
 // The GEMM of a packed linear map in the loaded weight format.
-hipError_t launch_gemm_packed(const lmop_ctx* c, GemmArgs& ga, const PackedW& W, int epi) {
-  ga.bq = W.qpack;
+// The launch starts at column c0 of the map, a multiple of 16 (a strip is
+// contiguous, so the columns from there on are a packed weight of their own).
+hipError_t launch_gemm_packed(const lmop_ctx* c, GemmArgs& ga, const PackedW& W, int epi,
+                              int c0 = 0) {
+  const size_t panels = (size_t)(c0 / 16) * (W.kp / 64);
   if (c->wfmt == LMOP_W_FP8_E4M3) {
-    ga.bsc = W.sscale;
+    ga.bq = W.qpack + panels * 256;
+    ga.bsc = W.sscale + c0;
     return launch_gemm_w8(c->stream, ga, epi);
   }
-  ga.bs = W.spack;
+  ga.bq = W.qpack + panels * 128;
+  ga.bs = W.spack + panels * 32;
   return launch_gemm_w4(c->stream, ga, epi);
 }
 
@@ -765,10 +773,19 @@ struct Need {
   size_t state_mask = 0;       // bytes of the automaton's state-mask table
 };
 
+int attn_tiles(int n_q, int G) { return (n_q * G + ATTN_QTILE - 1) / ATTN_QTILE; }
+
+// fp16 elements of "act": the MLP's activations, and before them, in the last
+// layer, the normalised last tokens
+size_t act_halves(const lmop_ctx* c, size_t T, size_t last) {
+  return std::max(T * c->f64, last * c->cfg.d_model);
+}
+
 // Device bytes of one pass's host-built arrays (see upload_batch)
-size_t batch_in_bytes(size_t T, size_t R, size_t W, size_t last, size_t head_rows) {
-  return T * 12 + R * sizeof(AttnRow) + W * sizeof(int2) + last * 4 +
-         head_rows * (sizeof(void*) + 4) + 16 * 8;
+size_t batch_in_bytes(size_t T, size_t R, size_t W, size_t last, size_t last_work,
+                      size_t head_rows) {
+  return T * 12 + R * sizeof(AttnRow) + W * sizeof(int2) + last * (8 + sizeof(AttnRow)) +
+         last_work * sizeof(int2) + head_rows * (sizeof(void*) + 4) + 16 * (last > 0 ? 11 : 8);
 }
 
 // (name, bytes) of every scratch buffer of a call with these maxima, in
@@ -780,14 +797,14 @@ std::vector<std::pair<const char*, size_t>> scratch_items(const lmop_ctx* c, con
   auto add = [&](const char* name, size_t bytes) { it.emplace_back(name, scratch_round(bytes)); };
   // a batch whose rows all have empty suffixes still reads one row of x
   const size_t T = std::max<size_t>(n.T, 1);
-  add("in", batch_in_bytes(T, n.R, n.W, n.last, n.head_rows));
+  const int G = c->cfg.n_heads / c->cfg.n_kv_heads;
+  add("in", batch_in_bytes(T, n.R, n.W, n.last, n.last * attn_tiles(1, G), n.head_rows));
   add("x", T * d * 4);
   add("h", T * d * 2);
   add("q", T * c->nq_dim * 2);
   add("att", T * c->nq_dim * 2);
-  add("act", T * c->f64 * 2);
+  add("act", act_halves(c, T, n.last) * 2);
   add("xlast", n.last * d * 4);
-  add("attlast", n.last * c->nq_dim * 2);
   add("own_kv", n.own_kv);
   if (n.head_rows > 0) {
     const size_t R = n.head_rows;
@@ -858,8 +875,6 @@ std::vector<std::pair<size_t, size_t>> make_batches(const std::vector<int>& len,
   }
   return out;
 }
-
-int attn_tiles(int n_q, int G) { return (n_q * G + ATTN_QTILE - 1) / ATTN_QTILE; }
 
 // The forward-pass maxima of a list of batches over entries of len[]
 void batch_need(const std::vector<int>& len, const std::vector<std::pair<size_t, size_t>>& batches,
@@ -954,15 +969,32 @@ struct Batch {
   const float* const* rowptr = nullptr;  // final hidden state of each head row
   const int32_t* state = nullptr;        // automaton state of each head row, or NULL
   // Tokens whose final hidden state is needed (`last`), or 0 = all tokens.
-  // With n_last > 0 the last layer's O-projection and MLP run on those tokens
-  // only, and their final hidden states land in ws "xlast" [n_last][d].
+  // With n_last > 0 the last layer's O-projection and MLP (and, where that
+  // saves enough, its Q projection and attention) run on those tokens only,
+  // and their final hidden states land in ws "xlast" [n_last][d].
   int n_last = 0;
-  // keys visible to the batch's query tokens, summed (for the attention FLOP count)
-  double visible_keys = 0;
+  // for the last layer's queries, one per token of `last`: position, attention
+  // row (query token = index in `last`) and work items
+  const int32_t* pos_last = nullptr;
+  const AttnRow* rows_last = nullptr;
+  const int2* work_last = nullptr;
+  int n_work_last = 0;
+  // keys visible to the batch's query tokens (to those of `last`), summed (for
+  // the attention FLOP count)
+  double visible_keys = 0, visible_last = 0;
   // a decode step (one token per live row): its launches are timed under
   // "decode_"-prefixed names, apart from the prefill passes
   bool decode = false;
 };
+
+// Tokens that the last layer's split of Q from K and V has to save.  The
+// split saves two thirds of the QKV launch (head ratio 4) and most of
+// attention, and costs a launch of 8 us for the selected rows' Q and, with one
+// query token per row, attention whose key walk is as long as before: at 1,000
+// tokens (8B shape, one prefix) both sides take the same time, at 400 tokens
+// and 9 rows too; 552 join rows of 41 tokens take 0.46 ms less (15.69 -> 15.23
+// with 4 layers), a 6,200-token prompt 0.3 ms less.
+constexpr int kQuerySplitTokens = 256;
 
 // One pass of all layers over the T tokens whose ids/positions/slots and row
 // descriptors are already on the device.
@@ -976,7 +1008,7 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
   LMOP_TRY(ws_get(c, "h", (size_t)T * d, &h));
   LMOP_TRY(ws_get(c, "q", (size_t)T * c->nq_dim, &q));
   LMOP_TRY(ws_get(c, "att", (size_t)T * c->nq_dim, &att));
-  LMOP_TRY(ws_get(c, "act", (size_t)T * c->f64, &act));
+  LMOP_TRY(ws_get(c, "act", act_halves(c, T, b.n_last), &act));
 
   LMOP_TRY(timed(c, "embed", 0, (double)T * d * 6, [&] {
     return launch_embed(c->stream, b.tok, T, c->emb, d, x);
@@ -990,14 +1022,30 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
     }));
     uint16_t* kc = b.own_kv + l * kv_layer;
     uint16_t* vt = kc + (size_t)b.own_cap * c->nkv_dim;
-    {
+    const bool last = l == cf.n_layers - 1 && b.n_last > 0;
+    // In the last layer every token's K and V are needed, but only the
+    // selected tokens' queries: the QKV projection is then two launches, K and
+    // V of all tokens and Q of the selected ones, and attention has one query
+    // token per row.  Every value is computed as in the whole launch, so the
+    // results are the same bits.  It pays where the tokens saved are worth the
+    // further launch (see kQuerySplitTokens).
+    const bool split_q = last && T - b.n_last >= kQuerySplitTokens;
+    int M = T;
+    float* xr = x;
+    uint16_t* ar = att;
+    if (last) {
+      M = b.n_last;
+      LMOP_TRY(ws_get(c, "xlast", (size_t)M * d, &xr));
+    }
+    // columns [c0, c1) of the fused QKV projection, c0 a multiple of 256
+    auto qkv = [&](const uint16_t* A, int rows, const int32_t* pos, int c0, int c1) {
       GemmArgs ga{};
-      ga.A = h;
+      ga.A = A;
       ga.lda = d;
-      ga.M = T;
-      ga.N = L.qkv.np;
+      ga.M = rows;
+      ga.N = round_up(c1, 256) - c0;
       ga.K = L.qkv.kp;
-      ga.pos = b.pos;
+      ga.pos = pos;
       ga.slot = b.slot;
       ga.rope = c->rope_tab;
       ga.qout = q;
@@ -1007,20 +1055,34 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
       ga.nq = cf.n_heads;
       ga.nkv = cf.n_kv_heads;
       ga.hd = hd;
-      const double flops = 2.0 * T * L.qkv.n * L.qkv.k;
-      const double bytes = (double)T * L.qkv.k * 2 + weight_bytes(c, L.qkv.n, L.qkv.k) +
-                           (double)T * L.qkv.n * 2;
-      LMOP_TRY(timed(c, gemm_name(c, "qkv", b.decode), flops, bytes,
-                     [&] { return launch_gemm_packed(c, ga, L.qkv, EPI_QKV); }));
+      ga.pair0 = c0 / 32;
+      ga.pair_end = c1 / 32;
+      const double n = c1 - c0;
+      const double flops = 2.0 * rows * n * L.qkv.k;
+      const double bytes =
+          (double)rows * L.qkv.k * 2 + weight_bytes(c, n, L.qkv.k) + (double)rows * n * 2;
+      return timed(c, gemm_name(c, "qkv", b.decode), flops, bytes,
+                   [&] { return launch_gemm_packed(c, ga, L.qkv, EPI_QKV, c0); });
+    };
+    if (split_q) {
+      // from the last multiple of 256 columns: where Q does not end at one, the
+      // few Q columns before K are written here too, and again by the next launch
+      LMOP_TRY(qkv(h, T, b.pos, c->nq_dim / 256 * 256, L.qkv.n));
+      LMOP_TRY(timed(c, "gather_rows", 0, (double)M * (d * 8 + d * 4), [&] {
+        return launch_gather_rows(c->stream, b.last, M, x, d, xr, h, d, act);
+      }));
+      LMOP_TRY(qkv(act, M, b.pos_last, 0, c->nq_dim));
+    } else {
+      LMOP_TRY(qkv(h, T, b.pos, 0, L.qkv.n));
     }
     AttnArgs aa{};
     aa.q = q;
     aa.ldq = c->nq_dim;
     aa.out = att;
     aa.ldo = c->nq_dim;
-    aa.rows = b.rows;
-    aa.work = b.work;
-    aa.n_work = b.n_work;
+    aa.rows = split_q ? b.rows_last : b.rows;
+    aa.work = split_q ? b.work_last : b.work;
+    aa.n_work = split_q ? b.n_work_last : b.n_work;
     aa.own_kv = b.own_kv;
     aa.own_cap = b.own_cap;
     aa.layer = l;
@@ -1028,20 +1090,17 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
     aa.nkv = cf.n_kv_heads;
     aa.hd = hd;
     // per visible (query token, key) pair and query head: q.k and p.v, 2 FLOP per dim each
-    const double attn_flops = 4.0 * hd * cf.n_heads * b.visible_keys;
+    const double attn_flops =
+        4.0 * hd * cf.n_heads * (split_q ? b.visible_last : b.visible_keys);
     LMOP_TRY(timed(c, b.decode ? "decode_attention" : "attention", attn_flops, 0,
                    [&] { return launch_attention(c->stream, aa); }));
-    // in the last layer only the selected tokens continue (their K/V are written above)
-    int M = T;
-    float* xr = x;
-    uint16_t* ar = att;
-    if (l == cf.n_layers - 1 && b.n_last > 0) {
-      LMOP_TRY(ws_get(c, "xlast", (size_t)b.n_last * d, &xr));
-      LMOP_TRY(ws_get(c, "attlast", (size_t)b.n_last * c->nq_dim, &ar));
-      LMOP_TRY(timed(c, "gather_rows", 0, (double)b.n_last * (d * 8 + c->nq_dim * 4), [&] {
-        return launch_gather_rows(c->stream, b.last, b.n_last, x, d, xr, att, c->nq_dim, ar);
+    // without the split the selected tokens are taken here; attention is done
+    // with q, which takes their rows
+    if (last && !split_q) {
+      ar = q;
+      LMOP_TRY(timed(c, "gather_rows", 0, (double)M * (d * 8 + c->nq_dim * 4), [&] {
+        return launch_gather_rows(c->stream, b.last, M, x, d, xr, att, c->nq_dim, ar);
       }));
-      M = b.n_last;
     }
     auto gemm2 = [&](const char* name, const void* A, int lda, const PackedW& W, int epi,
                      void* C, int ldc, int n_out) {
@@ -1072,6 +1131,11 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
   return LMOP_OK;
 }
 
+void add_work(std::vector<int2>& work, int row, int n_q, int G) {
+  const int tiles = attn_tiles(n_q, G);
+  for (int t = 0; t < tiles; ++t) work.push_back(make_int2(row, t));
+}
+
 // Uploads the host-built per-token and per-row arrays of one forward pass and
 // its head through staging slot k (which stage_begin has sized) and sets the
 // batch's device pointers; does not wait.  The arrays lie one after the other
@@ -1085,6 +1149,24 @@ lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t
                          const std::vector<const float*>& rowptr = {},
                          const std::vector<int32_t>& state = {}) {
   c->stage[k].used = 0;
+  // `last` holds the last token of every row that has tokens, in row order
+  std::vector<int32_t> pos_last;
+  std::vector<AttnRow> rows_last;
+  std::vector<int2> work_last;
+  if (!last.empty()) {
+    const int G = c->cfg.n_heads / c->cfg.n_kv_heads;
+    for (const AttnRow& r : rows) {
+      if (r.n_q == 0) continue;
+      const int i = (int)rows_last.size();
+      pos_last.push_back(pos[last[i]]);
+      b->visible_last += pos_last[i] + 1;
+      rows_last.push_back(r);
+      rows_last[i].own_q0 += r.n_q - 1;
+      rows_last[i].q_start = i;
+      rows_last[i].n_q = 1;
+      add_work(work_last, i, 1, G);
+    }
+  }
   size_t total = 0;
   auto place = [&](size_t bytes) {
     const size_t off = total;
@@ -1095,7 +1177,9 @@ lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t
   const size_t o_tok = place(bytes_of(tok)), o_pos = place(bytes_of(pos)),
                o_slot = place(bytes_of(slot)), o_rows = place(bytes_of(rows)),
                o_work = place(bytes_of(work)), o_last = place(bytes_of(last)),
-               o_rowptr = place(bytes_of(rowptr)), o_state = place(bytes_of(state));
+               o_rowptr = place(bytes_of(rowptr)), o_state = place(bytes_of(state)),
+               o_pos_last = place(bytes_of(pos_last)), o_rows_last = place(bytes_of(rows_last)),
+               o_work_last = place(bytes_of(work_last));
   char *d, *h;
   LMOP_TRY(ws_get(c, "in", total, &d));
   LMOP_TRY(stage_put(c, k, (const char*)nullptr, total, &h));
@@ -1110,6 +1194,9 @@ lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t
   put(o_last, last);
   put(o_rowptr, rowptr);
   put(o_state, state);
+  put(o_pos_last, pos_last);
+  put(o_rows_last, rows_last);
+  put(o_work_last, work_last);
   if (total > 0) HIP_OK(c, hipMemcpyAsync(d, h, total, hipMemcpyHostToDevice, c->stream));
   b->tok = (const int32_t*)(d + o_tok);
   b->pos = (const int32_t*)(d + o_pos);
@@ -1118,6 +1205,10 @@ lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t
   b->work = (const int2*)(d + o_work);
   b->last = (const int32_t*)(d + o_last);
   b->rowptr = (const float* const*)(d + o_rowptr);
+  b->pos_last = (const int32_t*)(d + o_pos_last);
+  b->rows_last = (const AttnRow*)(d + o_rows_last);
+  b->work_last = (const int2*)(d + o_work_last);
+  b->n_work_last = (int)work_last.size();
   b->state = state.empty() ? nullptr : (const int32_t*)(d + o_state);
   return LMOP_OK;
 }
@@ -1136,11 +1227,6 @@ void fill_segments(const lmop_prefix* p, AttnRow& r) {
       r.seg_cap[s] = chain[s]->cap;
       r.seg_start[s] = chain[s]->slot0;
     }
-}
-
-void add_work(std::vector<int2>& work, int row, int n_q, int G) {
-  const int tiles = attn_tiles(n_q, G);
-  for (int t = 0; t < tiles; ++t) work.push_back(make_int2(row, t));
 }
 
 // Enqueues the head over the batch's R rows, whose final hidden states are at
