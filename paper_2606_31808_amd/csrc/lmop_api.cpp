@@ -993,7 +993,7 @@ struct Batch {
 // query token per row, attention whose key walk is as long as before: at 1,000
 // tokens (8B shape, one prefix) both sides take the same time, at 400 tokens
 // and 9 rows too; 552 join rows of 41 tokens take 0.46 ms less (15.69 -> 15.23
-// with 4 layers), a 6,200-token prompt 0.3 ms less.
+// with 4 layers), a 6,200-token prompt about 0.2 ms less.
 constexpr int kQuerySplitTokens = 256;
 
 // One pass of all layers over the T tokens whose ids/positions/slots and row
