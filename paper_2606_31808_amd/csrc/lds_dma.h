@@ -9,6 +9,9 @@
 // followed by barrier() (all waves) before the LDS data is read.
 //
 // These kernels use M0 for nothing else; the asm sets it before each load.
+// The chip needs one wait state between a scalar write of M0 and an LDS load
+// that uses it (the compiler puts it before its own loads, not into asm), so
+// an s_nop, or another scalar instruction, stands between the two.
 #pragma once
 #include "common.h"
 
@@ -20,7 +23,7 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 LMOP_DEVICE void g2l16(const void* gaddr, void* lds_base) {
   const uint32_t m0 =
       __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)lds_base);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :
                : "v"(gaddr), "s"(m0)
                : "memory");
@@ -30,7 +33,7 @@ LMOP_DEVICE void g2l16(const void* gaddr, void* lds_base) {
 // registers) plus a per-lane 32-bit byte offset, and the LDS destination
 // given as a wave-uniform LDS address
 LMOP_DEVICE void g2l16_m0(const void* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(voff), "s"(sbase), "s"(lds_addr)
                : "memory");
