@@ -60,6 +60,7 @@
 // tiles, ordered in groups of GM token tiles so that concurrently running
 // tiles on an XCD share A and W panels in that XCD's L2.
 #include "common.h"
+#include "gemm_ring.h"
 #include "kernels.h"
 #include "lds_dma.h"
 
@@ -466,7 +467,7 @@ __global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(c
         // most the later ones are in flight
         if (MORE) {
           constexpr int FLY = NS - 2 - AHEAD;
-          if (PF_ALL > 0 && kt + NS - 1 >= KT - PFW)
+          if (PF_ALL > 0 && all_carry_prefetch(kt + NS - 1, FLY, KT, PFW))
             wait_vmcnt_lgkm0<FLY * (LOADS + 1)>();
           else
             wait_vmcnt_lgkm0<FLY * LOADS>();
