@@ -775,12 +775,6 @@ struct Need {
 
 int attn_tiles(int n_q, int G) { return (n_q * G + ATTN_QTILE - 1) / ATTN_QTILE; }
 
-// fp16 elements of "act": the MLP's activations, and before them, in the last
-// layer, the normalised last tokens
-size_t act_halves(const lmop_ctx* c, size_t T, size_t last) {
-  return std::max(T * c->f64, last * c->cfg.d_model);
-}
-
 // Device bytes of one pass's host-built arrays (see upload_batch)
 size_t batch_in_bytes(size_t T, size_t R, size_t W, size_t last, size_t last_work,
                       size_t head_rows) {
@@ -803,7 +797,7 @@ std::vector<std::pair<const char*, size_t>> scratch_items(const lmop_ctx* c, con
   add("h", T * d * 2);
   add("q", T * c->nq_dim * 2);
   add("att", T * c->nq_dim * 2);
-  add("act", act_halves(c, T, n.last) * 2);
+  add("act", T * c->f64 * 2);
   add("xlast", n.last * d * 4);
   add("own_kv", n.own_kv);
   if (n.head_rows > 0) {
@@ -996,6 +990,15 @@ struct Batch {
 // with 4 layers), a 6,200-token prompt about 0.2 ms less.
 constexpr int kQuerySplitTokens = 256;
 
+// Whether the last layer of a pass of T tokens, n_last of them selected,
+// computes Q and attention for those only.  Their normalised rows wait in
+// "act", which a narrow MLP (d_ff below d_model * n_last / T) makes too small;
+// such a pass takes the whole projection rather than more scratch.
+bool query_split(const lmop_ctx* c, int T, int n_last) {
+  return n_last > 0 && T - n_last >= kQuerySplitTokens &&
+         (size_t)n_last * c->cfg.d_model <= (size_t)T * c->f64;
+}
+
 // One pass of all layers over the T tokens whose ids/positions/slots and row
 // descriptors are already on the device.
 lmop_status forward(lmop_ctx* c, const Batch& b) {
@@ -1008,7 +1011,7 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
   LMOP_TRY(ws_get(c, "h", (size_t)T * d, &h));
   LMOP_TRY(ws_get(c, "q", (size_t)T * c->nq_dim, &q));
   LMOP_TRY(ws_get(c, "att", (size_t)T * c->nq_dim, &att));
-  LMOP_TRY(ws_get(c, "act", act_halves(c, T, b.n_last), &act));
+  LMOP_TRY(ws_get(c, "act", (size_t)T * c->f64, &act));
 
   LMOP_TRY(timed(c, "embed", 0, (double)T * d * 6, [&] {
     return launch_embed(c->stream, b.tok, T, c->emb, d, x);
@@ -1027,9 +1030,8 @@ lmop_status forward(lmop_ctx* c, const Batch& b) {
     // selected tokens' queries: the QKV projection is then two launches, K and
     // V of all tokens and Q of the selected ones, and attention has one query
     // token per row.  Every value is computed as in the whole launch, so the
-    // results are the same bits.  It pays where the tokens saved are worth the
-    // further launch (see kQuerySplitTokens).
-    const bool split_q = last && T - b.n_last >= kQuerySplitTokens;
+    // results are the same bits.
+    const bool split_q = last && query_split(c, T, b.n_last);
     int M = T;
     float* xr = x;
     uint16_t* ar = att;

@@ -48,3 +48,33 @@ def test_last_tokens_only(heads, kv_heads, head_dim, fmt, lens):
     assert out[4096][0].tobytes() == out[1][0].tobytes()
     ctx.release_prefix(pre)
     ctx.close()
+
+
+@pytest.mark.parametrize("d_ff,launches", [(64, 2), (128, 3)])
+def test_narrow_mlp(d_ff, launches):
+    """130 rows of 3 tokens save over 256 queries; with d_ff 64 the MLP's
+    buffer cannot hold their 130 x 256 normalised values, so the pass takes the
+    whole projection (one QKV launch per layer, no further one)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_31808_amd import lmop as L
+    shape = dataclasses.replace(SHAPES["tiny"], name="narrow", n_layers=2, d_ff=d_ff, vocab=640)
+    w = make_weights(shape, seed=d_ff)
+    ctx = L.Context(shape, device=0)
+    ctx.load_weights(w)
+    rng = np.random.default_rng(d_ff)
+    rows = [rng.integers(0, shape.vocab, size=3).astype(np.int32) for _ in range(130)]
+    offs = np.arange(0, 391, 3).astype(np.int64)
+    print("narrow MLP:", d_ff, flush=True)
+    ctx.set_profiling(1)
+    whole = ctx.eval_rows(np.concatenate(rows), offs, L.LMOP_ENUM, ALLOWED, no_dedup=True,
+                          debug_logits=True)
+    assert ctx.kernel_stats()["gemm_w4a16_qkv"]["launches"] == launches
+    ctx.set_profiling(0)
+    alone = ctx.eval_rows(np.concatenate(rows), offs, L.LMOP_ENUM, ALLOWED, no_dedup=True,
+                          debug_logits=True, max_batch_tokens=1)
+    assert np.array_equal(whole[1], alone[1])
+    assert whole[0].tobytes() == alone[0].tobytes()
+    ref = OracleLM(w, shape).eval_rows(None, rows, 1, ALLOWED, keep_logits=True)
+    compare(ref, *whole, f"d_ff {d_ff}")
+    ctx.close()

@@ -397,3 +397,24 @@ def test_plan_rows_host(tiny_w):
     dump = ctx.plan_rows(*args, debug_logits=True)
     assert dump["scratch_bytes"] >= pl["scratch_bytes"] + wl.n_rows * TINY.vocab * 4
     assert dump["min_workspace_bytes"] > pl["min_workspace_bytes"]
+
+
+@pytest.mark.parametrize("d,f,heads,least,whole", [
+    (1536, 64, 2, 87296, 3292928), (1024, 100, 1, 71424, 2268928), (2048, 128, 4, 105472, 4456192)])
+def test_narrow_mlp_workspace(d, f, heads, least, whole):
+    """Models whose MLP and heads are narrower than d_model: the last layer's
+    gathered rows need no scratch of their own, so workspaces of the size that
+    the activation buffers alone take run the call, and in one pass."""
+    import dataclasses
+    shape = dataclasses.replace(TINY, n_layers=1, d_model=d, n_heads=heads, n_kv_heads=1, d_ff=f,
+                                vocab=640)
+    ctx = _host_ctx(shape)
+    ctx.load_weights(make_weights(shape, seed=1))
+    args = (np.arange(256, dtype=np.int32), np.arange(0, 257, 4), L.LMOP_BOOL, [1, 2])
+    pl = ctx.plan_rows(*args, no_dedup=True)
+    assert pl["min_workspace_bytes"] <= least and pl["scratch_bytes"] <= whole
+    ctx.set_workspace(1 << 20, least)
+    _expect(L.LMOP_ERR_UNSUPPORTED, ctx.eval_rows, *args, no_dedup=True)  # planned; no device
+    ctx.set_workspace(1 << 20, whole)
+    assert ctx.plan_rows(*args, no_dedup=True)["batches"] == 1
+    ctx.close()
