@@ -589,20 +589,20 @@ __global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(c
 // ---------------------------------------------------------------- few tokens
 // The same product for few tokens, where dequantising is most of the work and
 // the strips alone do not fill the SIMDs (256 strips for N = 4096): a
-// workgroup of 16*MI tokens x FJ strips has 3 waves that only issue loads (a
+// workgroup of 16 tokens x FJ strips has 3 waves that only issue loads (a
 // wave that also converts is held up by each load), 8 that dequantise a
-// share of each stage's weight fragments each into LDS, and NC that only
-// multiply (each all tokens x FJ / NC strips, in the same order as above).
+// share of each stage's weight fragments each into LDS, and one that only
+// multiplies (in the same order as above).
 // One barrier per stage of KP panels: while stage kt is multiplied, stage
 // kt + 1 is converted and later ones are loaded.
 // Measured at 9 tokens (us, against the best shape of gemm_kernel): K 4096, N
 // 4096 9.8 -> 6.8; K 14336 24.3 -> 14.8; QKV (K 4096, N 6144) 9.8 -> 8.2.  A
 // stage of 512 features takes about 1,000 cycles: the converters' read,
 // convert and write chain and the barrier, then LDS traffic.
-template <int MI, int WF, int FJ, int NC, int KP>
+template <int WF, int FJ, int KP>
 struct SplitCfg {
-  static constexpr int BM = 16 * MI, BN = 16 * FJ, NP = 8, NLA = 2;
-  static constexpr int WAVES = 1 + NLA + NP + NC;
+  static constexpr int BM = 16, BN = 16 * FJ, NP = 8, NLA = 2;
+  static constexpr int WAVES = 1 + NLA + NP + 1;
   static constexpr int PANEL = BM * 128;
   static constexpr int WB = WF == WF_INT4 ? 512 : 1024;
   static constexpr int A_BYTES = KP * PANEL, C_BYTES = FJ * KP * WB;
@@ -638,12 +638,11 @@ LMOP_DEVICE void wait_stages(int n) {
   }
 }
 
-template <int MI, int WF, int EPI, int FJ, int NC, int KP>
-__global__ __launch_bounds__((64 * SplitCfg<MI, WF, FJ, NC, KP>::WAVES), 3) void gemm_split_kernel(const GemmArgs p) {
-  using C = SplitCfg<MI, WF, FJ, NC, KP>;
+template <int WF, int EPI, int FJ, int KP>
+__global__ __launch_bounds__((64 * SplitCfg<WF, FJ, KP>::WAVES), 3) void gemm_split_kernel(const GemmArgs p) {
+  using C = SplitCfg<WF, FJ, KP>;
   constexpr int BM = C::BM, BN = C::BN, NP = C::NP, NLA = C::NLA, NSA = C::NSA, NSW = C::NSW;
-  constexpr int FC = FJ / NC;  // strips of a consumer
-  static_assert(FJ % NC == 0 && (EPI == EPI_ADD_F32 || FC % 2 == 0), "pairs in one wave");
+  static_assert(EPI == EPI_ADD_F32 || FJ % 2 == 0, "pairs in one wave");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -809,29 +808,24 @@ __global__ __launch_bounds__((64 * SplitCfg<MI, WF, FJ, NC, KP>::WAVES), 3) void
   }
 
   // ---- consumer
-  const int f0 = (wave - 1 - NLA - NP) * FC;
   const uint32_t a_lane[2] = {(uint32_t)(c * 128 + ((g ^ swz(c)) * 16)),
                               (uint32_t)(c * 128 + (((4 + g) ^ swz(c)) * 16))};
-  f32x4 acc[FC][MI];
+  f32x4 acc[FJ];
 #pragma unroll
-  for (int f = 0; f < FC; ++f)
-#pragma unroll
-    for (int i = 0; i < MI; ++i) acc[f][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int f = 0; f < FJ; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
   barrier();
   uint32_t st = 0;
   for (int kt = 0; kt < KT; ++kt) {
     barrier();
     const char* fr = fb + (kt & 1) * C::FB + lane * 16;
     // (strip f, panel)'s fragments are at ((f * KP + panel) * 2 + kk) KB
-    f16x8 a[2 * KP][MI], w[2 * KP][FC];
+    f16x8 a[2 * KP], w[2 * KP][FJ];
 #pragma unroll
     for (int ks = 0; ks < 2 * KP; ++ks) {
 #pragma unroll
-      for (int f = 0; f < FC; ++f)
-        w[ks][f] = *(const f16x8*)(fr + (((f0 + f) * KP + (ks >> 1)) * 2 + (ks & 1)) * 1024);
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-        a[ks][i] = *(const f16x8*)(smem + st + a_lane[ks & 1] + (ks >> 1) * C::PANEL + i * 2048);
+      for (int f = 0; f < FJ; ++f)
+        w[ks][f] = *(const f16x8*)(fr + ((f * KP + (ks >> 1)) * 2 + (ks & 1)) * 1024);
+      a[ks] = *(const f16x8*)(smem + st + a_lane[ks & 1] + (ks >> 1) * C::PANEL);
     }
     // all reads before the first MFMA (the compiler would read, wait and
     // multiply step by step)
@@ -839,45 +833,38 @@ __global__ __launch_bounds__((64 * SplitCfg<MI, WF, FJ, NC, KP>::WAVES), 3) void
 #pragma unroll
     for (int ks = 0; ks < 2 * KP; ++ks)
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int f = 0; f < FC; ++f) acc[f][i] = mfma16x16x32(w[ks][f], a[ks][i], acc[f][i]);
+      for (int f = 0; f < FJ; ++f) acc[f] = mfma16x16x32(w[ks][f], a[ks], acc[f]);
     wait_vmcnt_lgkm0<0>();  // this stage is read, also where an MFMA was moved past the barrier
     st = st + C::A_BYTES == NSA * C::A_BYTES ? 0u : st + C::A_BYTES;
   }
-  const int mrow = m0 + c, ncol = n0 + 16 * f0 + 4 * g;
+  const int m = m0 + c, ncol = n0 + 4 * g;
   if constexpr (WF == WF_FP8) {
 #pragma unroll
-    for (int f = 0; f < FC; ++f) {
+    for (int f = 0; f < FJ; ++f) {
       const float4 sc = *(const float4*)(p.bsc + ncol + 16 * f);
-#pragma unroll
-      for (int i = 0; i < MI; ++i) acc[f][i] = acc[f][i] * f32x4{sc.x, sc.y, sc.z, sc.w};
+      acc[f] = acc[f] * f32x4{sc.x, sc.y, sc.z, sc.w};
     }
   }
+  if constexpr (EPI == EPI_ADD_F32) {
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    if constexpr (EPI == EPI_ADD_F32) {
+    for (int f = 0; f < FJ; ++f) add_residual(p, m, ncol + 16 * f, acc[f]);
+  } else {
 #pragma unroll
-      for (int f = 0; f < FC; ++f) add_residual(p, mrow + 16 * i, ncol + 16 * f, acc[f][i]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < FC / 2; ++t)
-        store_pair<EPI>(p, mrow + 16 * i, g, acc[2 * t][i], acc[2 * t + 1][i],
-                        ((n0 >> 4) + f0) / 2 + t);
-    }
+    for (int t = 0; t < FJ / 2; ++t)
+      store_pair<EPI>(p, m, g, acc[2 * t], acc[2 * t + 1], (n0 >> 5) + t);
   }
 }
 
-template <int MI, int WF, int EPI, int FJ, int NC, int KP>
+template <int WF, int EPI, int FJ, int KP>
 hipError_t launch_split(hipStream_t s, const GemmArgs& a) {
-  using C = SplitCfg<MI, WF, FJ, NC, KP>;
+  using C = SplitCfg<WF, FJ, KP>;
   const int tiles = ((a.M + C::BM - 1) / C::BM) * (a.N / C::BN);
   if (tiles == 0) return hipSuccess;
   static const hipError_t attr = hipFuncSetAttribute(
-      (const void*)gemm_split_kernel<MI, WF, EPI, FJ, NC, KP>,
+      (const void*)gemm_split_kernel<WF, EPI, FJ, KP>,
       hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gemm_split_kernel<MI, WF, EPI, FJ, NC, KP>), dim3(tiles),
+  hipLaunchKernelGGL((gemm_split_kernel<WF, EPI, FJ, KP>), dim3(tiles),
                      dim3(64 * C::WAVES), C::LDS, s, a);
   return hipGetLastError();
 }
@@ -956,9 +943,9 @@ hipError_t launch_epi(hipStream_t s, const GemmArgs& a) {
     case 8: return launch_cfg<1, WF, EPI, 1, 4, 8, 8, 1>(s, a);
     default:
       if constexpr (EPI == EPI_ADD_F32)
-        return launch_split<1, WF, EPI, 1, 1, 8>(s, a);
+        return launch_split<WF, EPI, 1, 8>(s, a);
       else
-        return launch_split<1, WF, EPI, 2, 1, 4>(s, a);
+        return launch_split<WF, EPI, 2, 4>(s, a);
   }
 }
 
