@@ -16,6 +16,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -25,7 +26,8 @@ if ROOT not in sys.path:
 
 PEAK_F16_TFLOPS = 2500.0   # MI355X dense fp16/bf16 MFMA
 PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
-GEMM_SRC = os.path.join(ROOT, "paper_2606_31808_amd", "csrc", "gemm.hip")
+CSRC = os.path.join(ROOT, "paper_2606_31808_amd", "csrc")
+GEMM_SRC = [os.path.join(CSRC, f) for f in ("gemm.hip", "gemm_ring.h", "lds_dma.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_w4a16_hbm_traffic.json")
 COPY_BYTES = 1 << 30       # plain copy used to calibrate the HBM byte counters
 # Kernel durations in the timed region come from HIP events around every
@@ -61,13 +63,14 @@ def gemm_roofline(stats):
 
 
 def _src_hash():
-    """SHA-256 prefix of the GEMM source's code: // comments, trailing blanks
+    """SHA-256 prefix of the GEMM sources' code: // comments, trailing blanks
     and empty lines are dropped, so that a comment edit does not void the
     recorded traffic counters while any change to the code does."""
     import hashlib
-    import re
-    with open(GEMM_SRC) as f:
-        lines = [re.sub(r"\s*//.*$", "", l).rstrip() for l in f]
+    lines = []
+    for src in GEMM_SRC:
+        with open(src) as f:
+            lines += [re.sub(r"\s*//.*$", "", l).rstrip() for l in f]
     code = "\n".join(l for l in lines if l)
     return hashlib.sha256(code.encode()).hexdigest()[:16]
 
@@ -90,12 +93,32 @@ def _bench_line(log_path):
     return json.loads(lines[-1])
 
 
+def _gemm_format_epi(name):
+    """(weight format, epilogue) of a weight GEMM's kernel name, else None:
+    gemm_kernel<MI, format, epilogue, ...>, gemm_split_kernel<format, epilogue,
+    ...>; format 1 = int4, 2 = FP8."""
+    m = re.search(r"\bgemm_(split_)?kernel<([^>]*)>", name)
+    if not m:
+        return None
+    args = [a.strip() for a in m[2].split(",")]
+    return tuple(args[:2] if m[1] else args[1:3])
+
+
 def _is_w4_gemm(name):
-    # gemm_kernel<MI, weight format, epilogue, ...>; format 1 = int4
-    if "gemm_kernel<" not in name:
-        return False
-    args = name.split("gemm_kernel<")[1].split(">")[0].split(",")
-    return len(args) >= 2 and args[1].strip() in ("1", "true")
+    return (_gemm_format_epi(name) or ("",))[0] == "1"
+
+
+def kernel_family(name):
+    """The kernel families of the MFMA summary; None for every other kernel."""
+    fe = _gemm_format_epi(name)
+    if fe:
+        if fe[0] != "1":
+            return "W8A16 GEMM (FP8 weights)"
+        return {"1": "W4A16 GEMM, residual add (o, down)", "2": "W4A16 GEMM, SwiGLU (gate/up)",
+                "4": "W4A16 GEMM, QKV + RoPE (qkv)"}[fe[1]]
+    if "head2_kernel<" in name or "head_few_kernel<" in name:
+        return "LM head GEMM"
+    return "attention" if "attn_kernel<" in name else None
 
 
 def _timed_gemm_rows(rows, n_timed):
@@ -167,24 +190,11 @@ def mfma_summary(root):
     gemm_ids = sorted(i for i, d in by_id.items() if _is_w4_gemm(d["name"]))[-n:]
     first = gemm_ids[0]
 
-    def family(name):
-        if _is_w4_gemm(name):
-            epi = name.split("gemm_kernel<")[1].split(",")[2].strip()
-            return {"1": "W4A16 GEMM, residual add (o, down)", "2": "W4A16 GEMM, SwiGLU (gate/up)",
-                    "4": "W4A16 GEMM, QKV + RoPE (qkv)"}.get(epi, epi)
-        if "gemm_kernel<" in name:
-            return "W8A16 GEMM (FP8 weights)"
-        if "head2_kernel" in name or "head_kernel" in name:
-            return "LM head GEMM"
-        if "attn_kernel" in name:
-            return "attention"
-        return None
-
     agg = {}
     for i, d in by_id.items():
         if i < first:
             continue
-        fam = family(d["name"])
+        fam = kernel_family(d["name"])
         if fam is None:
             continue
         a = agg.setdefault(fam, [0, 0.0, 0.0, 0.0])
