@@ -27,7 +27,7 @@ if ROOT not in sys.path:
 PEAK_F16_TFLOPS = 2500.0   # MI355X dense fp16/bf16 MFMA
 PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 CSRC = os.path.join(ROOT, "paper_2606_31808_amd", "csrc")
-GEMM_SRC = [os.path.join(CSRC, f) for f in ("gemm.hip", "gemm_ring.h", "lds_dma.h")]
+GEMM_SRC = [os.path.join(CSRC, f) for f in ("gemm.hip", "gemm_ring.h", "gemm_tiles.h", "lds_dma.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_w4a16_hbm_traffic.json")
 COPY_BYTES = 1 << 30       # plain copy used to calibrate the HBM byte counters
 # Kernel durations in the timed region come from HIP events around every

@@ -61,11 +61,12 @@
 // tiles on an XCD share A and W panels in that XCD's L2.
 #include "common.h"
 #include "gemm_ring.h"
+#include "gemm_tiles.h"
 #include "kernels.h"
 #include "lds_dma.h"
 
-#include <cmath>
 #include <type_traits>
+#include <utility>
 
 namespace lmop {
 
@@ -884,69 +885,28 @@ hipError_t launch_cfg(hipStream_t s, const GemmArgs& a) {
   return hipGetLastError();
 }
 
-// A tile shape and its measured time per 64-feature panel in ns: with one
-// workgroup on a CU (t1) and, where two fit, with two (t2).
-struct Tile {
-  int bm, bn, kp, occ;
-  float t1, t2;
-};
+template <int WF, int EPI, int I>
+hipError_t launch_tile(hipStream_t s, const GemmArgs& a) {
+  constexpr GemmTile t = kGemmTiles[I];
+  if constexpr (!t.offered(WF == WF_FP8, EPI == EPI_ADD_F32))
+    return hipErrorInvalidValue;  // never picked
+  else if constexpr (t.kk == 0)
+    return launch_split<WF, EPI, t.fj, t.kp>(s, a);
+  else
+    return launch_cfg<t.mi, WF, EPI, t.fj, t.nw, t.kp, t.kk, t.occ>(s, a);
+}
 
-// Estimated time of the GEMM's M x N tiles per 64-feature panel: rounds over
-// the 256 CUs, the last one with one workgroup a CU if they suffice.  Every
-// tile shape sums each output in the same order, so the choice never changes
-// a bit.  Measured against each other on M = 9 .. 16384 tokens at N = 4096
-// and 28672, the estimate picks the fastest shape or one within 5% of it.
-inline float tile_cost(const Tile& t, const GemmArgs& a) {
-  if ((a.K / 64) % t.kp != 0) return INFINITY;
-  const long tiles = (long)((a.M + t.bm - 1) / t.bm) * (a.N / t.bn);
-  const long round = 256 * t.occ, full = tiles / round, rem = tiles % round;
-  const float tf = t.occ == 2 ? t.t2 : t.t1;
-  return full * tf + (rem == 0 ? 0.f : rem <= 256 ? t.t1 : t.t2);
+template <int WF, int EPI, int... I>
+hipError_t launch_picked(hipStream_t s, const GemmArgs& a, std::integer_sequence<int, I...>) {
+  const int pick = pick_gemm_tile(WF == WF_FP8, EPI == EPI_ADD_F32, a.M, a.N, a.K);
+  hipError_t e = hipErrorInvalidValue;
+  (void)((pick == I && (e = launch_tile<WF, EPI, I>(s, a), true)) || ...);
+  return e;
 }
 
 template <int WF, int EPI>
 hipError_t launch_epi(hipStream_t s, const GemmArgs& a) {
-  constexpr bool I4 = WF == WF_INT4;
-  // large token tiles convert each weight for more tokens; small ones reach
-  // more CUs, and walk K in stages of several panels
-  static const Tile tiles[] = {
-      {128, 256, 1, 2, I4 ? 900.f : 1040.f, I4 ? 1620.f : 1590.f},
-      {128, 128, 1, 2, I4 ? 560.f : 500.f, I4 ? 943.f : 855.f},
-      {64, 128, 2, 2, I4 ? 330.f : 430.f, I4 ? 560.f : 540.f},
-      {64, 64, 2, 2, 215.f, 350.f},
-      {32, 128, 4, 1, I4 ? 225.f : 195.f, 0.f},
-      {32, 128, 1, 2, I4 ? 300.f : 250.f, I4 ? 415.f : 380.f},
-      {32, 64, 4, 2, I4 ? 140.f : 215.f, I4 ? 220.f : 240.f},
-      {16, 64, 4, 2, I4 ? 127.f : 112.f, I4 ? 200.f : 180.f},
-      {16, 64, 8, 1, I4 ? 105.f : 97.f, 0.f},
-      // split between waves: whole strip pairs where the epilogue needs them
-      EPI == EPI_ADD_F32 ? Tile{16, 16, 8, 1, 55.f, 0.f} : Tile{16, 32, 4, 1, 85.f, 0.f},
-  };
-  int best = 0;
-  float cost = INFINITY;
-  for (int i = 0; i < (int)(sizeof(tiles) / sizeof(tiles[0])); ++i) {
-    const float c = tile_cost(tiles[i], a);
-    if (c < cost) {
-      cost = c;
-      best = i;
-    }
-  }
-  switch (best) {
-    case 0: return launch_cfg<8, WF, EPI, 4, 4, 1, 1, 2>(s, a);
-    case 1: return launch_cfg<8, WF, EPI, 2, 4, 1, 1, 2>(s, a);
-    case 2: return launch_cfg<4, WF, EPI, 2, 4, 2, 2, 2>(s, a);
-    case 3: return launch_cfg<4, WF, EPI, 1, 4, 2, 2, 2>(s, a);
-    case 4: return launch_cfg<2, WF, EPI, 2, 4, 4, 4, 1>(s, a);
-    case 5: return launch_cfg<2, WF, EPI, 2, 4, 1, 1, 2>(s, a);
-    case 6: return launch_cfg<2, WF, EPI, 1, 4, 4, 4, 2>(s, a);
-    case 7: return launch_cfg<1, WF, EPI, 1, 4, 4, 4, 2>(s, a);
-    case 8: return launch_cfg<1, WF, EPI, 1, 4, 8, 8, 1>(s, a);
-    default:
-      if constexpr (EPI == EPI_ADD_F32)
-        return launch_split<WF, EPI, 1, 8>(s, a);
-      else
-        return launch_split<WF, EPI, 2, 4>(s, a);
-  }
+  return launch_picked<WF, EPI>(s, a, std::make_integer_sequence<int, kNumGemmTiles>{});
 }
 
 // ---------------------------------------------------------------- LM head

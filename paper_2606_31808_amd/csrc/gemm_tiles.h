@@ -1,0 +1,72 @@
+// The weight GEMM's tile shapes and the rule that picks one; plain C++, so
+// that the host can check which launch takes which shape.
+#pragma once
+#include <cmath>
+
+namespace lmop {
+
+// A tile of 16*mi tokens x 16*fj*nw columns: nw waves side by side along N,
+// each with all tokens and fj strips of 16 columns, kp panels of 64 features
+// per ring stage, kk steps of 32 features per phase, occ workgroups per CU.
+// kk = 0: gemm_split_kernel (loaders, converters and a multiplier).
+// t1[format], t2[format]: measured time per 64-feature panel in ns with one
+// workgroup on a CU and, where two fit, with two (format 0 = int4, 1 = FP8);
+// 0 = not offered in this format, because another shape is never slower.
+struct GemmTile {
+  int mi, fj, nw, kp, kk, occ;
+  float t1[2], t2[2];
+  // the split shapes fit one kind of epilogue: the residual add takes single
+  // strips, the others need pairs of strips in one wave
+  bool add = true, pairs = true;
+  constexpr int bm() const { return 16 * mi; }
+  constexpr int bn() const { return 16 * fj * nw; }
+  constexpr bool offered(bool fp8, bool add_epilogue) const {
+    return t1[fp8] > 0.f && (add_epilogue ? add : pairs);
+  }
+};
+
+// large token tiles convert each weight for more tokens; small ones reach
+// more CUs, and walk K in stages of several panels
+constexpr GemmTile kGemmTiles[] = {
+    {8, 4, 4, 1, 1, 2, {900.f, 1040.f}, {1620.f, 1590.f}},
+    {8, 2, 4, 1, 1, 2, {560.f, 500.f}, {943.f, 855.f}},
+    {4, 2, 4, 2, 2, 2, {330.f, 430.f}, {560.f, 540.f}},
+    {4, 1, 4, 2, 2, 2, {215.f, 215.f}, {350.f, 350.f}},
+    {2, 2, 4, 4, 4, 1, {0.f, 195.f}, {0.f, 0.f}},
+    {2, 2, 4, 1, 1, 2, {300.f, 250.f}, {415.f, 380.f}},
+    {2, 1, 4, 4, 4, 2, {140.f, 0.f}, {220.f, 0.f}},
+    {1, 1, 4, 4, 4, 2, {127.f, 112.f}, {200.f, 180.f}},
+    {1, 1, 4, 8, 8, 1, {105.f, 97.f}, {0.f, 0.f}},
+    {1, 1, 1, 8, 0, 1, {55.f, 55.f}, {0.f, 0.f}, true, false},
+    {1, 2, 1, 4, 0, 1, {85.f, 85.f}, {0.f, 0.f}, false, true},
+};
+constexpr int kNumGemmTiles = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
+
+// Estimated time of the GEMM's M x N tiles per 64-feature panel: rounds over
+// the 256 CUs, the last one with one workgroup a CU if they suffice.
+inline float gemm_tile_cost(const GemmTile& t, bool fp8, int M, int N, int K) {
+  if ((K / 64) % t.kp != 0) return INFINITY;
+  const long tiles = (long)((M + t.bm() - 1) / t.bm()) * (N / t.bn());
+  const long round = 256 * t.occ, full = tiles / round, rem = tiles % round;
+  const float tf = t.occ == 2 ? t.t2[fp8] : t.t1[fp8];
+  return full * tf + (rem == 0 ? 0.f : rem <= 256 ? t.t1[fp8] : t.t2[fp8]);
+}
+
+// The shape (index into kGemmTiles) with the least estimated time for M
+// tokens, N columns (a multiple of 256) and K features (of 64).  Every shape
+// sums each output in the same order, so the choice never changes a bit.
+inline int pick_gemm_tile(bool fp8, bool add_epilogue, int M, int N, int K) {
+  int best = 0;
+  float cost = INFINITY;
+  for (int i = 0; i < kNumGemmTiles; ++i) {
+    if (!kGemmTiles[i].offered(fp8, add_epilogue)) continue;
+    const float c = gemm_tile_cost(kGemmTiles[i], fp8, M, N, K);
+    if (c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
+}  // namespace lmop

@@ -1,6 +1,6 @@
-"""The GEMM's tile shapes: every shape the dispatch can pick, at the edges of
-its token tile, gives a row the same bits as any other shape does, and the
-oracle's logits."""
+"""The GEMM's tile shapes: every shape the dispatch can pick (which launches
+take which is checked on the host by test_gemm_tile_rule.py) gives a row the
+same bits as any other shape does, and the oracle's logits."""
 import dataclasses
 
 import numpy as np
@@ -19,6 +19,22 @@ SHAPE = dataclasses.replace(SHAPES["tiny"], name="tiles", n_layers=2, d_model=51
                             n_kv_heads=2, d_ff=1024, vocab=640)
 LENS = [1, 16, 7, 40, 64, 100, 33, 128]
 ALLOWED = np.array([3, 77, 400, 639], np.int32)
+
+
+TOKENS = [1, 15, 16, 17, 64, 65, 129, 513, 1025, 2049, 4100, 8200, 16384]
+MODELS = [("int4_g32", 1024), ("int4_g32", 688), ("fp8_e4m3", 1024)]
+# widths and token counts whose launches take the shapes that SHAPE's do not
+OTHER = [("int4_g32", (320, 4, 2, 64, 256), 1), ("int4_g32", (320, 4, 2, 64, 256), 33),
+         ("int4_g32", (256, 8, 2, 128, 688), 100), ("fp8_e4m3", (320, 32, 8, 128, 688), 2049),
+         ("fp8_e4m3", (256, 8, 8, 128, 256), 1300), ("fp8_e4m3", (256, 4, 2, 64, 14336), 513),
+         ("fp8_e4m3", (3072, 4, 2, 64, 256), 1300), ("fp8_e4m3", (3072, 4, 2, 64, 256), 4100)]
+ALONE = 23  # rows that also get a pass each
+
+
+def _other(widths):
+    d, heads, kv, hd, d_ff = widths
+    return dataclasses.replace(SHAPE, d_model=d, n_heads=heads, n_kv_heads=kv, head_dim=hd,
+                               d_ff=d_ff)
 
 
 def _rows(tokens):
@@ -40,8 +56,7 @@ def L():
     return lmop
 
 
-@pytest.fixture(scope="module", params=[("int4_g32", 1024), ("int4_g32", 688), ("fp8_e4m3", 1024)],
-                ids=["int4", "int4-688", "fp8"])
+@pytest.fixture(scope="module", params=MODELS, ids=["int4", "int4-688", "fp8"])
 def model(request, L):
     fmt, d_ff = request.param
     shape = dataclasses.replace(SHAPE, d_ff=d_ff)
@@ -51,9 +66,22 @@ def model(request, L):
     return w, shape, ctx
 
 
-@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 64, 65, 129, 513, 1025, 2049, 4100, 8200, 16384])
+@pytest.mark.parametrize("tokens", TOKENS)
 def test_tile_shapes_agree(model, L, tokens):
-    w, shape, ctx = model
+    _check(L, *model, tokens)
+
+
+@pytest.mark.parametrize("fmt,widths,tokens", OTHER)
+def test_other_widths_agree(L, fmt, widths, tokens):
+    shape = _other(widths)
+    w = make_weights(shape, seed=33, fmt=fmt)
+    ctx = L.Context(shape, device=0)
+    ctx.load_weights(w)
+    _check(L, w, shape, ctx, tokens)
+    ctx.close()
+
+
+def _check(L, w, shape, ctx, tokens):
     rng = np.random.default_rng([5, tokens])
     lens = _rows(tokens)
     offs = np.zeros(len(lens) + 1, np.int64)
@@ -66,7 +94,7 @@ def test_tile_shapes_agree(model, L, tokens):
                              debug_logits=len(o) <= 24)
 
     whole, logits = run(offs, toks, 1 << 15)  # one pass (2,048 rows at most)
-    few = min(len(lens), 23)
+    few = min(len(lens), ALONE)
     alone, _ = run(offs[:few + 1], toks[:offs[few]], 1)  # one pass per row
     for f in ("value", "logprob", "logprob_full"):
         assert np.array_equal(whole[f][:few], alone[f]), f
