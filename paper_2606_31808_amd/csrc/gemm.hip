@@ -373,8 +373,8 @@ __global__ __launch_bounds__((64 * NW), ((OCC * NW + 3) / 4)) void gemm_kernel(c
   };
   constexpr int PH = 2 * KP / KK;      // phases of a stage, KK steps of 32 features each
   constexpr int SLOTS = KK * MI * FJ;  // MFMAs of a phase
-  constexpr int LOADS = C::LOADS, AHEAD = PH == 1 ? 0 : C::AHEAD;
-  static_assert((2 * KP) % KK == 0, "phases of a stage");
+  constexpr int LOADS = C::LOADS, AHEAD = C::AHEAD;
+  static_assert((2 * KP) % KK == 0 && PH >= 2, "a stage is freed while its last phase runs");
   // panels whose codes a phase needs (with KK = 1 two phases share a panel)
   constexpr int NPC = KK == 1 ? 1 : KK / 2;
   // dequantisation of one phase's KK * FJ weight fragments in DP pieces of
