@@ -1151,11 +1151,12 @@ lmop_status upload_batch(lmop_ctx* c, int k, Batch* b, const std::vector<int32_t
                          const std::vector<const float*>& rowptr = {},
                          const std::vector<int32_t>& state = {}) {
   c->stage[k].used = 0;
-  // `last` holds the last token of every row that has tokens, in row order
+  // `last` holds the last token of every row that has tokens, in row order; the
+  // arrays made from it are for a pass that splits its last layer's queries off
   std::vector<int32_t> pos_last;
   std::vector<AttnRow> rows_last;
   std::vector<int2> work_last;
-  if (!last.empty()) {
+  if (query_split(c, (int)tok.size(), (int)last.size())) {
     const int G = c->cfg.n_heads / c->cfg.n_kv_heads;
     for (const AttnRow& r : rows) {
       if (r.n_q == 0) continue;
