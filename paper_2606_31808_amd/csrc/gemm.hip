@@ -1109,9 +1109,9 @@ hipError_t launch_head2(hipStream_t s, const GemmArgs& a) {
 }
 
 // ---------------------------------------------------------------- LM head, few rows
-// The same for at most 64 rows, where the head is a stream over its weight
-// (1.05 GB for V = 128256, d = 4096) and the ring's barriers and its 256
-// token rows of loads keep it at 5.0 TB/s.  One wave per vocabulary tile with
+// The same for at most 64 rows (see head_streams), where the head is a stream
+// over its weight (1.05 GB for V = 128256, d = 4096) and the ring's barriers
+// and its 256 token rows of loads keep it at 5.0 TB/s.  One wave per vocabulary tile with
 // all rows (F groups of 16): the weight goes straight from memory to
 // registers, D steps of 8 KB ahead per wave and no barrier anywhere, and the
 // token rows come from L2.  Every logit is accumulated in the same order as
@@ -1216,11 +1216,11 @@ hipError_t launch_gemm_f16(hipStream_t s, const GemmArgs& a, int epi) {
     return hipErrorInvalidValue;
   // per-lane token-row offsets are 32-bit byte offsets within one tile's rows
   if ((size_t)512 * a.ldb * 2 >= (size_t(1) << 31)) return hipErrorInvalidValue;
-  // Up to 64 rows one wave holds all of them (more do not fit its registers);
-  // at 65 rows the ring kernel takes 235 us where 64 rows here take 214.
-  if (a.N <= 16) return launch_head_few<1, 4>(s, a);
-  if (a.N <= 32) return launch_head_few<2, 3>(s, a);
-  if (a.N <= 64) return launch_head_few<4, 2>(s, a);
+  if (head_streams(a.N, a.M)) {
+    if (a.N <= 16) return launch_head_few<1, 4>(s, a);
+    if (a.N <= 32) return launch_head_few<2, 3>(s, a);
+    return launch_head_few<4, 2>(s, a);
+  }
   // A workgroup's time barely depends on how many of its token rows are
   // real, so the tile that needs fewer token tiles wins; a full 320-token
   // tile runs about 10% longer than a full 256-token one.  Each logit's

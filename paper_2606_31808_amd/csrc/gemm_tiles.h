@@ -1,5 +1,5 @@
-// The weight GEMM's tile shapes and the rule that picks one; plain C++, so
-// that the host can check which launch takes which shape.
+// The weight GEMM's tile shapes and the rules that pick one, and the LM head's
+// kernel; plain C++, so that the host can check which launch takes which.
 #pragma once
 #include <cmath>
 
@@ -67,6 +67,25 @@ inline int pick_gemm_tile(bool fp8, bool add_epilogue, int M, int N, int K) {
     }
   }
   return best;
+}
+
+// Whether the LM head streams its weight through registers (head_few_kernel)
+// or takes the LDS ring (head2_kernel).  The ring has a workgroup per pair of
+// 128-entry vocabulary tiles, so up to 512 tiles (V = 65,536) it runs one round
+// of the 256 CUs, in a time that neither V nor the rows change much, and twice
+// that from there on.  The stream has a wave per tile, which slows down with
+// every group of 16 rows.  Measured, us, stream against ring at d = 4096:
+//   V = 128256: 9 rows 155 / 213, 32: 160 / 219, 64: 212 / 232
+//   V = 66048: 16 rows 109 / 204, 32: 124 / 210, 64: 195 / 221
+//   V = 50304: 1 row 101 / 106, 16: 105 / 105, 20: 111 / 108, 64: 192 / 114
+//   V = 32000: 17 rows 103 / 105, 32: 117 / 107, 64: 190 / 113
+//   V = 16384: 20 rows 104 / 106, 24: 107 / 106, 28: 110 / 106
+//   V = 2048: 17 rows 92 / 103, 32: 105 / 105, 64: 173 / 110
+// so below 65,536 the line is at 16 to 32 rows; at d = 2048 it lies a few rows
+// higher.  65 rows do not fit a wave's registers.
+constexpr bool head_streams(int rows, int vocab) {
+  const int tiles = (vocab + 127) / 128;
+  return rows <= (tiles > 512 ? 64 : tiles > 256 ? 16 : tiles > 128 ? 20 : tiles > 16 ? 24 : 32);
 }
 
 }  // namespace lmop

@@ -14,6 +14,7 @@ SOURCE = """
 extern "C" int pick(int fp8, int add, int M, int N, int K) {
   return lmop::pick_gemm_tile(fp8, add, M, N, K);
 }
+extern "C" int head_streams(int rows, int vocab) { return lmop::head_streams(rows, vocab); }
 extern "C" int tiles() { return lmop::kNumGemmTiles; }
 extern "C" int offered(int i, int fp8, int add) { return lmop::kGemmTiles[i].offered(fp8, add); }
 """

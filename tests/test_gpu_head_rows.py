@@ -1,7 +1,7 @@
 """The LM head by number of rows: the register-streaming kernel (up to 16, 32
-and 64 rows) and the LDS-ring kernel give a row the same bits, and the
-oracle's logits, for widths that are not whole prefetch rounds and a
-vocabulary that is not whole tiles."""
+and 64 rows; at most 32 for vocabularies below 65,536) and the LDS-ring kernel
+give a row the same bits, and the oracle's logits, for widths that are not
+whole prefetch rounds and a vocabulary that is not whole tiles."""
 import dataclasses
 
 import numpy as np
@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 ALLOWED = np.array([0, 5, 640, 1000], np.int32)
 
 
-@pytest.mark.parametrize("d_model,vocab", [(64, 1001), (320, 1155), (512, 2048)])
+@pytest.mark.parametrize("d_model,vocab", [(64, 1001), (320, 1155), (512, 2048), (64, 65665),
+                                           (320, 66001)])
 def test_head_kernels_agree(d_model, vocab):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
