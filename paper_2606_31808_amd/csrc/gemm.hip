@@ -34,16 +34,23 @@
 // longer than an LDS access) and read codes two phases ahead.
 //
 // Measured against the loop before (wait, read, convert, multiply; token
-// tiles of 128, 64 and 32 rows by 256 columns), same card, us per launch:
-//   K = 4096, N = 4096 (O):      9 tokens 36.6 -> 9.8, 160: 37.7 -> 16.4,
-//     500: 39.1 -> 26.3, 1000: 52.4 -> 41.0, 2048: 73.4 -> 68.2
-//   K = 14336, N = 4096 (down):  9: 119.6 -> 24.6, 160: 121.5 -> 47.9,
-//     500: 123.3 -> 78.4, 1000: 160.5 -> 129, 2048: 235 -> 208
-//   K = 4096, N = 28672 (gate/up): 9: 36.8 -> 15.6, 60: 37.8 -> 23.7,
-//     2048: 366 -> 358, 16384: 2814 -> 2752
-// Up to a few hundred tokens what is left is dequantisation (13 VALU per 8
-// weights and token tile); at 16384 tokens the card's power limit (1.4
-// PFLOP/s on N(0, 0.02) weights; the fp16 library product reaches 1.46).
+// tiles of 128, 64 and 32 rows by 256 columns), same card, weights from
+// memory, the shape that the rule picks (up to 16 tokens mostly the kernel for
+// few tokens below), us per launch:
+//   K = 4096, N = 4096 (O):      9 tokens 36.4 -> 6.5, 60: 37.4 -> 9.8,
+//     160: 38.2 -> 17.3, 500: 39.0 -> 25.7, 1000: 52.0 -> 41.4, 2048: 79.8 -> 75.4
+//   K = 14336, N = 4096 (down):  9: 120.7 -> 15.0, 60: 122.5 -> 26.1,
+//     160: 122.6 -> 51.1, 500: 123.9 -> 77.3, 1000: 162.6 -> 130, 2048: 244 -> 211
+//   K = 4096, N = 28672 (gate/up): 9: 36.4 -> 16.1, 60: 38.1 -> 23.3,
+//     160: 62.3 -> 54.8, 1000: 201 -> 200, 2048: 382 -> 368, 16384: 2947 -> 2868
+// A layer's four projections together are faster at every size measured (1 to
+// 16384 tokens, 8B and 1B widths, both formats); single ones of 1,500 to 4,096
+// tokens are up to 7% slower (QKV of 1500: 87 -> 91-94, down of 3000: 310 -> 325).
+// At 16384 tokens the card's power limit bounds it (1.2-1.4 PFLOP/s on such
+// weights; the fp16 library product reaches 1.46).  Below a few hundred tokens
+// MFMAs and conversion are less than half of a launch: a 64x128 tile alone on
+// a CU takes 330 ns per panel of 16 MFMAs a wave (107 ns) with the VALU mostly
+// behind them; what the rest is has not been measured.
 //
 // The MFMA takes the weight fragment as its A operand and the activations
 // as its B operand, so the accumulator holds C^T: every lane owns 4
@@ -1116,8 +1123,8 @@ hipError_t launch_head2(hipStream_t s, const GemmArgs& a) {
 // registers, D steps of 8 KB ahead per wave and no barrier anywhere, and the
 // token rows come from L2.  Every logit is accumulated in the same order as
 // above.  Measured (us, d 4096 / d 2048, against the ring): 9 rows 213 ->
-// 155 / 128 -> 87 (6.8 TB/s, what a read of this card's memory reaches), 32
-// rows 218 -> 160 / 134 -> 94, 64 rows 231 -> 214 / 143 -> 120.
+// 155 / 132 -> 82 (6.8 TB/s at d 4096, what a read of this card's memory
+// reaches), 32 rows 219 -> 160 / 137 -> 85, 64 rows 232 -> 212 / 150 -> 115.
 template <int F, int D>
 __global__ __launch_bounds__(256, 2) void head_few_kernel(const GemmArgs p) {
   constexpr int MI = 8;

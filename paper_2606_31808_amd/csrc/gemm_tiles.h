@@ -43,7 +43,12 @@ constexpr GemmTile kGemmTiles[] = {
 constexpr int kNumGemmTiles = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
 
 // Estimated time of the GEMM's M x N tiles per 64-feature panel: rounds over
-// the 256 CUs, the last one with one workgroup a CU if they suffice.
+// the 256 CUs, the last one with one workgroup a CU if they suffice.  The
+// pipeline's fill and the epilogue (3-4 us of a launch) are left out, and one
+// table serves the three epilogues.  Over 23 token counts from 1 to 16384 and
+// the projections of the 8B and 1B widths the shape picked is the fastest or
+// within 5% of it in 158 of 184 launches in int4 and 176 in FP8, at worst 12%
+// slower (1B QKV of 400-1,000 tokens, O of 700 and of 4,096).
 inline float gemm_tile_cost(const GemmTile& t, bool fp8, int M, int N, int K) {
   if ((K / 64) % t.kp != 0) return INFINITY;
   const long tiles = (long)((M + t.bm() - 1) / t.bm()) * (N / t.bn());

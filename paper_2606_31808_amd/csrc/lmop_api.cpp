@@ -983,11 +983,16 @@ struct Batch {
 
 // Tokens that the last layer's split of Q from K and V has to save.  The
 // split saves two thirds of the QKV launch (head ratio 4) and most of
-// attention, and costs a launch of 8 us for the selected rows' Q and, with one
-// query token per row, attention whose key walk is as long as before: at 1,000
-// tokens (8B shape, one prefix) both sides take the same time, at 400 tokens
-// and 9 rows too; 552 join rows of 41 tokens take 0.46 ms less (15.69 -> 15.23
-// with 4 layers), a 6,200-token prompt about 0.2 ms less.
+// attention, and costs a launch for the selected rows' Q and, with one query
+// token per row, attention whose key walk is as long as before.  Whole calls
+// of a one-layer model with a 512-token prefix, us, whole -> split, by tokens
+// saved:
+//   8B widths, one row: 79: 229 -> 228, 179: 240 -> 231, 249: 241 -> 231,
+//     511: 261 -> 240, 999: 291 -> 258, 3999: 639 -> 383
+//   1B widths, one row: 129: 159 -> 162, 249: 165 -> 165, 399: 171 -> 169,
+//     699: 183 -> 172, 3999: 377 -> 261; rows of 8 tokens, 112: 168 -> 169,
+//     217: 183 -> 185, 350: 238 -> 235, 609: 220 -> 229, 1225: 272 -> 261
+// 256 is where the narrower shape stops losing; the wider one gains from 130.
 constexpr int kQuerySplitTokens = 256;
 
 // Whether the last layer of a pass of T tokens, n_last of them selected,
