@@ -41,9 +41,9 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def gemm_roofline(stats):
+def gemm_roofline(stats, recorded=""):
     """Dominant kernel family: the weight GEMMs (all four projections), W4A16
-    or, with FP8 weights, W8A16."""
+    or, with FP8 weights, W8A16.  recorded: see recorded_workload."""
     fp8 = any(n.startswith("gemm_w8a16") for n in stats)
     fam = "gemm_w8a16" if fp8 else "gemm_w4a16"
     names = [n for n in stats if n.startswith(fam)]
@@ -56,7 +56,7 @@ def gemm_roofline(stats):
     algo_bytes = sum(stats[n]["bytes"] for n in names) / timed
     return {"bound": "mfma", "kernel": f"{fam} (qkv, o, gate/up, down)", "achieved": ach,
             "peak": PEAK_F16_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_F16_TFLOPS,
-            "traffic": None if fp8 else measured_traffic(),
+            "traffic": None if fp8 else measured_traffic(TRAFFIC_FILE, recorded),
             "algorithmic_bytes_per_launch": algo_bytes,
             "launches": sum(stats[n]["launches"] for n in names), "timed_launches": timed,
             "avg_launch_ms": ms / timed, "flops_per_launch": fl / timed}
@@ -75,15 +75,25 @@ def _src_hash():
     return hashlib.sha256(code.encode()).hexdigest()[:16]
 
 
-def measured_traffic():
-    """HBM bytes per W4A16 GEMM launch from the committed PMC summary, if it was
-    taken on the current kernel source; otherwise None."""
+def recorded_workload(args):
+    """The workload name under which counters may have been recorded for this
+    run, or "" where an option changes which launches it makes."""
+    plain = (args.rows is None and not args.batch_tokens and not args.limit and not args.cascade
+             and not args.workspace_gb and args.weights == "int4_g32")
+    return args.workload if plain else ""
+
+
+def measured_traffic(path, recorded):
+    """HBM bytes per W4A16 GEMM launch from a committed PMC summary, if it was
+    taken on this workload and the current kernel sources; otherwise None."""
     try:
-        with open(TRAFFIC_FILE) as f:
+        with open(path) as f:
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    return t["bytes_per_launch"] if t.get("gemm_src_sha256_16") == _src_hash() else None
+    if t["workload"] != recorded or t.get("gemm_src_sha256_16") != _src_hash():
+        return None
+    return t["bytes_per_launch"]
 
 
 def _bench_line(log_path):
@@ -161,7 +171,7 @@ def pmc_summary(root):
     kw = COPY_BYTES / (cw * 1024.0)
     fetch_b = f_kib * 1024.0 * kf
     write_b = w_kib * 1024.0 * kw
-    out = {"gemm_src_sha256_16": _src_hash(), "launches": f_n, "fetch_bytes_per_launch": fetch_b,
+    out = {"gemm_src_sha256_16": _src_hash(), "workload": "filter_8b", "launches": f_n, "fetch_bytes_per_launch": fetch_b,
            "write_bytes_per_launch": write_b, "bytes_per_launch": fetch_b + write_b,
            "copy_scale_fetch": kf, "copy_scale_write": kw,
            "copy_fetch_kib": cf, "copy_write_kib": cw}
@@ -258,7 +268,7 @@ def head_roofline(stats):
 DECODE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "decode_gemm_map_int_8b_traffic.json")
 
 
-def decode_roofline(stats):
+def decode_roofline(stats, recorded=""):
     """Integer/automaton decode steps: one forward over every live row of a
     decode group per step, so each decode-step GEMM streams all its weights
     for the few thousand rows still decoding.  The bound is whichever roof
@@ -279,14 +289,7 @@ def decode_roofline(stats):
     tfl = fl / (ms * 1e-3) / 1e12
     ridge = PEAK_F16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
     mfma = fl / by > ridge
-    traffic = None
-    try:
-        with open(DECODE_TRAFFIC_FILE) as f:
-            t = json.load(f)
-        if t.get("gemm_src_sha256_16") == _src_hash():
-            traffic = t["bytes_per_launch"]
-    except (OSError, ValueError):
-        pass
+    traffic = measured_traffic(DECODE_TRAFFIC_FILE, recorded)
     ach, peak, unit = (tfl, PEAK_F16_TFLOPS, "TFLOP/s") if mfma else (gbs, PEAK_HBM_GBS, "GB/s")
     return {"kernel": "decode-step W4A16 GEMMs (qkv, o, gate/up, down)",
             "bound": "mfma" if mfma else "hbm", "achieved": ach, "peak": peak, "unit": unit,
@@ -632,9 +635,9 @@ def main():
                         "rows": wl.n_rows, "kept_by_first": cascade.get("kept"),
                         "first_ms": cascade.get("first_ms"),
                         "second_ms": cascade.get("second_ms")}} if args.cascade else {}),
-        "roofline": gemm_roofline(stats),
+        "roofline": gemm_roofline(stats, recorded_workload(args)),
         "head_roofline": head_roofline(stats),
-        **({"decode_roofline": dec} if (dec := decode_roofline(stats)) else {}),
+        **({"decode_roofline": dec} if (dec := decode_roofline(stats, recorded_workload(args))) else {}),
         "pass_rooflines": pass_rooflines(stats),
         "load_weights_s": t_load, "set_prefix_ms": t_prefix * 1e3,
         # device memory: what the library held at most (weights, prefix KV,

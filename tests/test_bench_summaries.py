@@ -1,6 +1,8 @@
 """The profile summaries of bench.py: every GEMM, head and attention kernel of
 the sources has a family, and the timed launches are the last ones of all W4A16
 GEMM kernels, not of one of them."""
+import argparse
+import json
 import os
 import re
 
@@ -46,3 +48,23 @@ def test_timed_rows_count_split_launches(few):
     rows += [{"Kernel_Name": "other", "Dispatch_Id": str(2 * i + 1)} for i in range(16)]
     got = [int(r["Dispatch_Id"]) for r in bench._timed_gemm_rows(rows[::-1], 10)]
     assert got == list(range(12, 32, 2))
+
+
+@pytest.mark.parametrize("change,known", [
+    ({}, True), ({"workload": "filter_1b"}, False), ({"rows": 100}, False), ({"limit": 5}, False),
+    ({"cascade": True}, False), ({"batch_tokens": 4096}, False), ({"workspace_gb": 8.0}, False),
+    ({"weights": "fp8_e4m3"}, False), ({"head_restricted": True}, True)])
+def test_traffic_is_of_the_recorded_workload(tmp_path, change, known):
+    """The counters' bytes per launch go with the run that they were taken on."""
+    args = argparse.Namespace(workload="filter_8b", rows=None, batch_tokens=0, limit=0,
+                              cascade=False, workspace_gb=0.0, weights="int4_g32",
+                              head_restricted=False)
+    vars(args).update(change)
+    f = tmp_path / "t.json"
+    f.write_text(json.dumps({"workload": "filter_8b", "bytes_per_launch": 7.0,
+                             "gemm_src_sha256_16": bench._src_hash()}))
+    got = bench.measured_traffic(str(f), bench.recorded_workload(args))
+    assert got == (7.0 if known else None)
+    f.write_text(json.dumps({"workload": "filter_8b", "bytes_per_launch": 7.0,
+                             "gemm_src_sha256_16": "0"}))
+    assert bench.measured_traffic(str(f), "filter_8b") is None
