@@ -664,8 +664,8 @@ lmop_status pack(lmop_ctx* c, const lmop_qmat* const* srcs, int n_src, const std
 }
 
 // The same for FP8 weights: E4M3 codes [n][k] and fp32 row scales [n] of up
-// to three sources -> 2 KB tiles per 64 columns x 32 features, fp32 scales in
-// packed column order.
+// to three sources -> strips of 16 columns x panels of 64 features (1 KB each),
+// fp32 scales in packed column order.
 lmop_status pack_fp8(lmop_ctx* c, const lmop_qmat* const* srcs, int n_src,
                      const std::vector<int32_t>& colmap, int n_logical, int k, bool on_device,
                      PackedW* out) {
